@@ -108,18 +108,18 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
     uint32_t next = 0;   // position in this wave's ray sequence (the same in all lanes)
     uint32_t ray_j = 0;  // position of this lane's ray in the sequence
     uint32_t ray_i = 0;  // index of this lane's ray in the launch
-    bool has = false;
+    tr.m_has = tr.m_blas = 0ull;
     // A finished ray's result stays in its lane until the next refill round
     // (or the wave's end), where all finished lanes place theirs together.
-    bool pend = false;
+    uint64_t m_pend = 0ull;
     uint32_t stalled = 0u;  // rounds since a ray of this wave last finished or was taken
     auto word = [&](int w) -> uint32_t {
         if (MODE == rgt::kRender && !ANY) {
             // the render's closest hits carry their float32 t to shading
-            if (w == 0) return __float_as_uint(tr.found ? tr.best : INFINITY);
+            if (w == 0) return __float_as_uint(tr.found() ? tr.best : INFINITY);
             return w == 1 ? tr.h.inst : tr.h.prim;
         }
-        if (ANY) return w == 0 ? (tr.found ? 1u : 0u) : (w == 1 ? tr.h.inst : tr.h.prim);
+        if (ANY) return w == 0 ? (tr.found() ? 1u : 0u) : (w == 1 ? tr.h.inst : tr.h.prim);
         return w == 0 ? tr.h.inst : tr.h.prim;
     };
     // word w of a ray goes to ...
@@ -158,12 +158,12 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
         const uint32_t cnt = n - first < 64u ? n - first : 64u;
         return cnt >= 64u ? ~0ull : ((1ull << cnt) - 1ull);
     };
-    // Places the results of lanes with `pend` (all lanes together), then
+    // Places the results of the lanes in m_pend (all lanes together), then
     // writes out complete packets; with `all`, writes out every slot.
     auto place = [&](bool all) {
         const uint32_t q = ray_j >> 6;
         const int s = (int)(q & (kStageSlots - 1));
-        if (pend) {
+        if (rgt::lane_in(m_pend)) {
             if (sown[s] == q) {
 #pragma unroll
                 for (int w = 0; w < K; ++w) sw[(s * K + w) * 64 + (ray_j & 63)] = word(w);
@@ -174,8 +174,8 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
 #pragma unroll
                 for (int w = 0; w < K; ++w) store(w, i, word(w));
             }
-            pend = false;
         }
+        m_pend = 0ull;
         wave_sync();
 #pragma unroll
         for (int k = 0; k < kStageSlots; ++k) {
@@ -235,22 +235,23 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
         }
     };
     while (true) {
-        // every ballot and every update of `next` below is executed by all
-        // lanes together, so `next` stays uniform across the wave
-        const uint64_t need = __ballot(!has);
+        // every ballot and every update of `next` and of the masks below is
+        // executed by all lanes together, so they stay uniform across the wave
+        const uint64_t need = ~tr.m_has;
         const int n_need = __popcll(need);
-        bool took = false;
+        bool took_any = false;
         if (n_need >= refill) {
             if (K > 0) place(false);
             claim(next, (uint32_t)n_need);
-            if (!has) {
+            bool took = false, live = false;
+            if (rgt::lane_in(need)) {
                 // this lane's rank among the idle lanes
                 const uint32_t j = next + __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
                 const uint32_t pkt = (j >> 6) < q_end ? spkt[(j >> 6) & (kStageSlots - 1)] : ~0u;
                 const uint32_t idx = pkt * 64 + (j & 63);
                 if (pkt < n_packets && idx < n) {
-                    if (K == 0 && pend) write_result();
+                    if (K == 0 && rgt::lane_in(m_pend)) write_result();
                     rgt::Ray R;
                     R.o[0] = a.ray[0][idx]; R.o[1] = a.ray[1][idx]; R.o[2] = a.ray[2][idx];
                     R.d[0] = a.ray[3][idx]; R.d[1] = a.ray[4][idx]; R.d[2] = a.ray[5][idx];
@@ -263,48 +264,37 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
                         tr.tlas_nodes = reinterpret_cast<const RgNode<W> *>(J.nodes);
                         tr.recs = J.recs;
                     }
-                    has = tr.begin(R);
+                    live = tr.begin(R);
                     if (OPT) tr.rmask = a.ray_mask ? (uint32_t)a.ray_mask[idx] : a.mask;
-                    pend = !has;  // empty interval: a miss without traversal
                     took = true;
                 }
             }
+            const uint64_t m_took = rgt::ballot(took), m_live = rgt::ballot(live);
+            tr.m_has |= m_live;
+            tr.m_blas &= ~m_took;
+            m_pend = (m_pend & ~m_took) | (m_took & ~m_live);  // empty interval: a miss without traversal
+            took_any = m_took != 0ull;
             next += n_need;
         }
-        if (__ballot(has) == 0) {
+        if (tr.m_has == 0ull) {
             // no lane holds a ray after a refill attempt of all 64 lanes: the
             // wave is done once its claims have run past the last packet
             if (out_of_work) break;
             continue;
         }
-        // Which kinds of unit run this round: inner nodes whenever a lane
-        // has one; leaves and instance entries (each a long stretch of code
-        // that runs for the whole wave if any lane needs it) once enough
-        // lanes wait for one, or when nothing else is left.  A lane that
-        // waits keeps its state; every round runs at least one kind present.
-        const uint32_t my = has ? tr.kind() : 0u;
-        const int n_inner = __popcll(__ballot(my == rgt::kUnitInner));
-        const int n_leaf = __popcll(__ballot(my == rgt::kUnitLeaf));
-        const int n_inst = __popcll(__ballot(my == rgt::kUnitInst));
-        uint32_t run = n_inner ? rgt::kUnitInner : 0u;
-        if (n_leaf && (n_leaf >= leaf_batch || n_inner == 0)) run |= rgt::kUnitLeaf;
-        if (n_inst && (n_inst >= inst_batch || run == 0)) run |= rgt::kUnitInst;
-        const bool fin = (run & my) != 0u && tr.step();  // my == 0 for lanes without a ray
-        if (fin) {
-            has = false;
-            pend = true;
-        }
+        const uint64_t fin = tr.round(leaf_batch, inst_batch);
+        m_pend |= fin;
         // loop bound: a wave whose rays stop finishing (only a corrupt
         // hierarchy can make a traversal cycle) gives up on them
-        if (__ballot(fin || took) != 0ull) {
+        if (fin != 0ull || took_any) {
             stalled = 0u;
         } else if (++stalled > rgt::kMaxSteps) {
-            if (has) pend = true;
-            has = false;
+            m_pend |= tr.m_has;
+            tr.m_has = 0ull;
         }
     }
     if (K > 0) place(true);
-    else if (pend) write_result();
+    else if (rgt::lane_in(m_pend)) write_result();
     if (claims && lane == 0) {
         __builtin_amdgcn_s_waitcnt(0);  // this wave's claims have come back
         if (atomicAdd(a.work + 1, 1u) == n_waves - 1u) {
