@@ -39,6 +39,15 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// A wave-uniform 64-bit value in scalar registers.  readfirstlane gives an
+// int: each half goes through uint32_t, or a set bit 31 of the low half would
+// fill the high half with ones.
+__device__ inline uint64_t uniform64(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Persistent traversal: each wave walks its own sequence of 64-ray packets,
 // and lanes whose ray has finished take the next rays of that sequence
 // together, once at least `refill` lanes are idle.  Rays of a packet stay
@@ -182,8 +191,7 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
             const uint32_t o = __builtin_amdgcn_readfirstlane(sown[k]);
             if (o == ~0u) continue;
             const uint64_t m = smask[k];
-            const uint64_t mu = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(m >> 32)) << 32) |
-                                __builtin_amdgcn_readfirstlane((uint32_t)m);
+            const uint64_t mu = uniform64(m);
             const uint32_t pkt = __builtin_amdgcn_readfirstlane(spkt[k]);
             if (all || mu == full_mask(pkt)) {
                 flush_slot(k, pkt, mu);
@@ -220,8 +228,7 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
             const uint32_t o = __builtin_amdgcn_readfirstlane(sown[k]);
             if (K > 0 && o != ~0u) {  // a straggler: write out what it has
                 const uint64_t m = smask[k];
-                const uint64_t mu = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(m >> 32)) << 32) |
-                                    __builtin_amdgcn_readfirstlane((uint32_t)m);
+                const uint64_t mu = uniform64(m);
                 flush_slot(k, __builtin_amdgcn_readfirstlane(spkt[k]), mu);
                 wave_sync();
             }
