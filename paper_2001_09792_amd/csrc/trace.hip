@@ -64,7 +64,8 @@ __device__ inline uint64_t uniform64(uint64_t v) {
 // memory operations first, so no claim of this launch can land after that).
 // Only long launches claim: in a short one the counter's traffic at the
 // start and at the end costs more than the imbalance it removes, and every
-// packet goes out interleaved.
+// packet goes out interleaved.  In a launch with fewer than 64 rays per wave
+// each wave takes one packet of fewer rays.
 template <int W, bool ANY, int MODE, bool OPT>
 __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refill, int lds_depth, int leaf_batch,
                                                          int inst_batch) {
@@ -74,11 +75,26 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
     // a device count never exceeds the launch size (the queue capacity)
     // (a launch holds fewer than 2^31 rays: positions and indices fit 32 bits)
     const uint32_t n = (uint32_t)(a.count ? ((int64_t)*a.count < a.n ? (int64_t)*a.count : a.n) : a.n);
-    const uint32_t n_packets = (n + 63) >> 6;
     // wave-uniform values kept in scalar registers
     const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave in the block
     const uint32_t wave = blockIdx.x * (rgt::kThreads / 64) + wib;
     const uint32_t n_waves = gridDim.x * (rgt::kThreads / 64);
+    // Rays per packet: 64, or fewer (a power of two, down to one) in a launch
+    // with fewer than 64 rays per wave, so that the rays spread over all the
+    // waves the launch has.  Such a launch lasts as long as its slowest wave,
+    // and a wave's time is the number of its rounds times the latency of a
+    // round: a node fetch and a chain of dependent instructions for each kind
+    // of unit that any of its lanes is at.  Fewer rays per wave mean fewer
+    // rounds with several kinds, and the chip idles otherwise.  Two-level
+    // scene, width 4, closest hit of random rays, 64-ray packets -> this rule:
+    // 64 rays 66 -> 37 us, 1,000 rays 78 -> 37, 16,384 rays 112 -> 76, 100,000
+    // rays 118 -> 94 (400,000 rays fill every wave: unchanged).
+    const uint32_t per_wave = (n + n_waves - 1u) / n_waves;
+    uint32_t psh = per_wave <= 1u ? 0u : 32u - (uint32_t)__builtin_clz(per_wave - 1u);
+    psh = psh > 6u ? 6u : psh;
+    const uint32_t psize = 1u << psh;
+    const uint32_t n_packets = (n + psize - 1u) >> psh;
+    if (psh < 6u) leaf_batch = inst_batch = 1;  // nothing to gain from lanes that wait for others
     // long launches (kClaimMin packets per wave or more): interleaved packets
     // per wave, the packets they cover, the rest claimed; shorter ones take
     // every packet interleaved and touch no counter
@@ -156,15 +172,15 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
     // together; uniform arguments).
     auto flush_slot = [&](int s, uint32_t pkt, uint64_t m) {
         if ((m >> lane) & 1ull) {
-            const uint32_t i = pkt * 64 + lane;
+            const uint32_t i = (pkt << psh) + lane;
 #pragma unroll
             for (int w = 0; w < K; ++w) store(w, i, sw[(s * K + w) * 64 + lane]);
         }
     };
-    // Rays of launch packet pkt: 64, fewer for the batch's last packet.
+    // Rays of launch packet pkt: psize, fewer for the launch's last packet.
     auto full_mask = [&](uint32_t pkt) -> uint64_t {
-        const uint32_t first = pkt * 64;
-        const uint32_t cnt = n - first < 64u ? n - first : 64u;
+        const uint32_t first = pkt << psh;
+        const uint32_t cnt = n - first < psize ? n - first : psize;
         return cnt >= 64u ? ~0ull : ((1ull << cnt) - 1ull);
     };
     // Places the results of the lanes in m_pend (all lanes together), then
@@ -239,6 +255,7 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
             }
             wave_sync();
             q_end = q + 1;
+            if (psh < 6u) out_of_work = true;  // one packet per wave, taken whole
         }
     };
     while (true) {
@@ -247,7 +264,12 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
         const uint64_t need = ~tr.m_has;
         const int n_need = __popcll(need);
         bool took_any = false;
-        if (n_need >= refill) {
+        // Nothing is left to take once a claim came back empty: finished rays
+        // then keep their results until the wave ends.  (Looking for work
+        // again in every round of a wave's tail cost about 100 instructions
+        // and eight LDS round trips per round: camera and AO rays over 10M
+        // triangles 6.96 -> 5.65 ms, a 1080p depth-4 frame 2.02 -> 1.69 ms.)
+        if (n_need >= refill && !out_of_work) {
             if (K > 0) place(false);
             claim(next, (uint32_t)n_need);
             bool took = false, live = false;
@@ -256,8 +278,8 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
                 const uint32_t j = next + __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
                 const uint32_t pkt = (j >> 6) < q_end ? spkt[(j >> 6) & (kStageSlots - 1)] : ~0u;
-                const uint32_t idx = pkt * 64 + (j & 63);
-                if (pkt < n_packets && idx < n) {
+                const uint32_t idx = (pkt << psh) + (j & 63);
+                if (pkt < n_packets && (j & 63) < psize && idx < n) {
                     if (K == 0 && rgt::lane_in(m_pend)) write_result();
                     rgt::Ray R;
                     R.o[0] = a.ray[0][idx]; R.o[1] = a.ray[1][idx]; R.o[2] = a.ray[2][idx];
@@ -282,6 +304,10 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
             m_pend = (m_pend & ~m_took) | (m_took & ~m_live);  // empty interval: a miss without traversal
             took_any = m_took != 0ull;
             next += n_need;
+            // the wave's last rays: its time is now its slowest ray's, and
+            // lanes waiting for others only add rounds (400,000 random rays
+            // 192 -> 157 us, 2.2M AO rays any hit with options 0.87 -> 0.69 ms)
+            if (out_of_work) leaf_batch = inst_batch = 1;
         }
         if (tr.m_has == 0ull) {
             // no lane holds a ray after a refill attempt of all 64 lanes: the
@@ -415,9 +441,11 @@ int rg_cu_count() {
 
 namespace {
 
+// Blocks of a launch over at most n rays: as many as the chip holds, and no
+// more waves than rays (short launches put fewer rays in a wave).
 unsigned persistent_blocks(int64_t n, int waves_per_cu) {
     int64_t want = (int64_t)rg_cu_count() * waves_per_cu / (rgt::kThreads / 64);
-    int64_t need = rg_blocks(n, rgt::kThreads);
+    int64_t need = rg_blocks(n, rgt::kThreads / 64);
     return (unsigned)(need < want ? need : want);
 }
 
