@@ -409,20 +409,24 @@ __global__ void __launch_bounds__(256) k_refine(RefineArgs a) {
 
 // Launch parameters per family of calls (RG_TUNE_*): refill threshold,
 // resident waves per CU, LDS stack entries per lane, lanes waiting at leaves
-// / instance entries before a wave runs that code.  Incoherent ray batches
-// gain from waiting lanes; the coherent rays of frames do not.  Every launch
-// takes at most the waves its variant keeps resident: the closest-hit
-// variant of frames fits 4 per SIMD, the any-hit one 5 at widths 2 and 4.
-// The engine runs a pass's any-hit launch beside the next pass's
-// closest-hit launch, and there the any-hit launch's fifth wave per SIMD
-// pays; single frames and batches gain nothing from it.  The engine's
-// passes mix the rays of many frames and depths: like incoherent batches
-// they gain from lanes waiting at leaves and instance entries, and from
-// refilling later (a measured sweep: refill 20..28 with leaf batch 12 best).
+// / instance entries before a wave runs that code (short launches and the
+// tails of long ones run without waiting, see k_trace).  Every launch takes
+// at most the waves its variant keeps resident.
+//
+// Large launches of incoherent rays (trace calls, the engine's mixed passes)
+// run best with 16 waves per CU although 20 fit: the units that 20 waves hold
+// in flight (64 lanes x 112 bytes each) push each other out of the 32 KB L1.
+// Camera and AO rays over 10M triangles, ms at 12 / 16 / 20 waves: 6.40 / 6.22
+// / 6.70 with refill 16, 6.55 / 6.09 / 6.47 with refill 24 (which costs 2.2M
+// any-hit rays 1.5%); without waiting lanes (batching 1 / 1) 6.70 / 6.45 / 6.80.  A served stream of 24 requests
+// at 12 / 16 / 20 waves: 12.6 / 12.3 / 12.7 ms.  Frames, coherent at first,
+// are within 2% of each other from 16 to 24 waves and refill 8 to 24; lanes
+// waiting at leaves for 12 others cost them up to 60%, for 4 others they gain
+// 1-2% (24 frames 1.82 -> 1.79 ms, 1080p depth-4 frame 1.59 -> 1.57 ms).
 rg_trace_tune g_tune[RG_TUNE_SCOPES] = {
-    {16, 20, 16, 12, 6},  // RG_TUNE_TRACE: rg_trace_closest / any / counts (5 waves per SIMD fit)
-    {8, 16, 16, 1, 1},    // RG_TUNE_FRAME: rg_render, rg_batch_render
-    {24, 20, 16, 12, 6},  // RG_TUNE_ENGINE: rg_engine_step
+    {16, 16, 16, 12, 6},  // RG_TUNE_TRACE: rg_trace_closest / any / counts
+    {16, 20, 16, 4, 2},   // RG_TUNE_FRAME: rg_render, rg_batch_render
+    {24, 16, 16, 12, 6},  // RG_TUNE_ENGINE: rg_engine_step
 };
 
 }  // namespace
