@@ -65,18 +65,24 @@ __device__ inline void camera_dir(const CamF &k, int W, int H, int64_t pixel, fl
     normalize3(d);
 }
 
-__global__ void k_camera_rays(rg_camera cam, int W, int H, float *o0, float *o1, float *o2, float *d0, float *d1,
-                              float *d2, float *tmin, float *tmax) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    int64_t n = (int64_t)W * H;
-    if (i >= n) return;
+struct CamRays {
+    float *a[8];
+};
+__device__ inline void camera_ray(const rg_camera &cam, int W, int H, int64_t i, const CamRays &r) {
     CamF k = camera_basis(cam);
     float d[3];
     camera_dir(k, W, H, i, d);
-    o0[i] = k.eye[0]; o1[i] = k.eye[1]; o2[i] = k.eye[2];
-    d0[i] = d[0]; d1[i] = d[1]; d2[i] = d[2];
-    tmin[i] = 0.0f;
-    tmax[i] = INFINITY;
+    for (int q = 0; q < 3; ++q) {
+        r.a[q][i] = k.eye[q];
+        r.a[3 + q][i] = d[q];
+    }
+    r.a[6][i] = 0.0f;
+    r.a[7][i] = INFINITY;
+}
+
+__global__ void k_camera_rays(rg_camera cam, int W, int H, CamRays r) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < (int64_t)W * H) camera_ray(cam, W, H, i, r);
 }
 
 // ------------------------------------------------------ hit geometry
@@ -135,22 +141,6 @@ __device__ inline void put_ray(float *const ray[8], uint32_t j, const float o[3]
     ray[6][j] = tmin; ray[7][j] = tmax;
 }
 
-// Appends `cnt` (0..2) entries per lane with one atomic per wave; returns
-// this lane's first slot.
-__device__ inline uint32_t wave_append(uint32_t *counter, uint32_t cnt) {
-    uint64_t b1 = __ballot(cnt >= 1u), b2 = __ballot(cnt >= 2u);
-    int lane = threadIdx.x & 63;
-    uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    uint32_t before = (uint32_t)(__popcll(b1 & lt) + __popcll(b2 & lt));
-    uint32_t total = (uint32_t)(__popcll(b1) + __popcll(b2));
-    uint64_t active = __ballot(1);
-    int leader = __ffsll((long long)active) - 1;
-    uint32_t base = 0;
-    if (lane == leader && total > 0) base = atomicAdd(counter, total);
-    base = __shfl(base, leader, 64);
-    return base + before;
-}
-
 // Block-wide append of two counts per thread (0..2 to `a`, 0..1 to `b`):
 // ballot ranks inside each wave, wave totals in LDS, one atomic per counter
 // per block.  Every thread of the block must call it.
@@ -197,11 +187,27 @@ __device__ inline uint32_t find_job(const RgJobDev *jobs, int n_jobs, uint32_t p
     return (uint32_t)lo;
 }
 
+// Clears pixel p's accumulators.
+__device__ inline void accum_clear(unsigned long long *acc, uint64_t p) {
+    for (int q = 0; q < 3; ++q) acc[3 * p + q] = 0ull;
+}
+
+// Counters of a wavefront render at the start of its first pass: n_rays
+// queued in ray queue 0, everything else zero.
+__device__ inline void start_counters(unsigned long long *stat, uint32_t *counts, uint32_t n_rays) {
+    for (int k = 0; k < 4; ++k) stat[k] = 0ull;
+    counts[0] = n_rays;
+    for (int k = 1; k < 8; ++k) counts[k] = 0u;
+}
+
+// The camera rays of every frame of a batch, its pixels' accumulators and
+// its counters cleared on the way.
 __global__ void k_camera_batch(const RgJobDev *__restrict__ jobs, int n_jobs, int64_t total, RgQueue q,
-                               uint32_t *count) {
+                               unsigned long long *acc, unsigned long long *stat, uint32_t *counts) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i == 0) *count = (uint32_t)total;
+    if (i == 0) start_counters(stat, counts, (uint32_t)total);
     if (i >= total) return;
+    accum_clear(acc, (uint64_t)i);
     uint32_t j = find_job(jobs, n_jobs, (uint32_t)i);
     const RgJobDev &J = jobs[j];
     CamF k = camera_basis(J.cam);
@@ -345,12 +351,31 @@ __global__ void __launch_bounds__(kShadeT) k_shade(ShadeArgs a) {
     }
 }
 
-__global__ void k_shadow_resolve(RgShadowQ sq, const uint32_t *count, unsigned long long *acc) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= (int64_t)*count) return;
-    if (sq.occ[i]) return;
-    float v[3] = {sq.pend[0][i], sq.pend[1][i], sq.pend[2][i]};
-    accum_add(acc, sq.pix[i], v);
+// The direct term of the unoccluded shadow rays of pass `pass`; persistent
+// (the queue's capacity is the worst case, usually a hundred times its
+// entries: 33 million threads to look at the last of five counts took 28 us,
+// this takes 5).  Its first thread closes the pass: what was traced goes into
+// the statistics (and to counts[5], counts[6], for a capture of the pass),
+// this pass's ray queue and the other parity's shadow queue become empty for
+// the next shading.  Three launches of one thread each did that before.
+__global__ void __launch_bounds__(kT) k_shadow_resolve(RgShadowQ sq, uint32_t *counts, int64_t pass, int64_t n_max,
+                                                       unsigned long long *acc, unsigned long long *stat) {
+    const uint32_t n = counts[2 + (pass & 1)];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const uint32_t traced = counts[pass & 1];
+        stat[0] += traced;
+        stat[1] += n;
+        counts[5] = traced;
+        counts[6] = n;
+        counts[pass & 1] = 0u;
+        counts[2 + ((pass + 1) & 1)] = 0u;
+    }
+    const int64_t m = (int64_t)n < n_max ? (int64_t)n : n_max;
+    for (int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kT) {
+        if (sq.occ[i]) continue;
+        float v[3] = {sq.pend[0][i], sq.pend[1][i], sq.pend[2][i]};
+        accum_add(acc, sq.pix[i], v);
+    }
 }
 
 __global__ void k_resolve_batch(const unsigned long long *acc, const RgJobDev *__restrict__ jobs, int n_jobs,
@@ -362,32 +387,6 @@ __global__ void k_resolve_batch(const unsigned long long *acc, const RgJobDev *_
     for (int c = 0; c < 3; ++c) J.image[3 * local + c] = (float)((double)acc[3 * i + c] * (1.0 / 4294967296.0));
 }
 
-__global__ void k_zero_u64(unsigned long long *p, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-}
-
-__global__ void k_stat_add(unsigned long long *stat, const uint32_t *count) { *stat += *count; }
-
-// Between a pass's closest-hit launch and its shading: the rays it traced
-// go into the statistics, and the next pass's queue count and the shadow
-// queue count start at zero (one launch instead of three).
-__global__ void k_pass_counts(unsigned long long *stat, const uint32_t *count_in, uint32_t *count_out,
-                              uint32_t *count_shadow) {
-    *stat += *count_in;
-    *count_out = 0u;
-    *count_shadow = 0u;
-}
-
-// Frame record and materials written through kernel arguments: nothing
-// for the host to keep alive, nothing to wait for, capturable.
-__global__ void k_put_job(RgJobDev *jobs, RgTlasRef *tlas, uint32_t slot, RgJobDev J, RgTlasRef T) {
-    if (threadIdx.x == 0) {
-        jobs[slot] = J;
-        tlas[slot] = T;
-    }
-}
-
 constexpr int kMatChunk = 64;
 struct MatChunk {
     RgMat m[kMatChunk];
@@ -396,19 +395,48 @@ __global__ void k_put_mats(RgMat *dst, MatChunk c, int n) {
     if ((int)threadIdx.x < n) dst[threadIdx.x] = c.m[threadIdx.x];
 }
 
-// Reserves n consecutive queue entries for a frame's camera rays: *base =
-// old count.
-__global__ void k_reserve(uint32_t *count, uint32_t n, uint32_t *base) {
-    if (threadIdx.x == 0) *base = atomicAdd(count, n);
+// A frame's record and first materials written through kernel arguments:
+// nothing for the host to keep alive, nothing to wait for, capturable.
+// first: the only frame of a render (its rays are queue 0's, the counters
+// start over); otherwise reserves entries for its camera rays in the queue
+// whose count is counts[queue], leaving their start in counts[4].
+struct PutFrame {
+    RgJobDev *jobs;
+    RgTlasRef *tlas;
+    RgMat *mats;
+    unsigned long long *stat;
+    uint32_t *counts;
+    RgJobDev J;
+    RgTlasRef T;
+    uint32_t slot;
+    int queue, n_mats;
+    bool first;
+    MatChunk m;
+};
+__global__ void __launch_bounds__(kMatChunk) k_put_frame(PutFrame a) {
+    if ((int)threadIdx.x < a.n_mats) a.mats[threadIdx.x] = a.m.m[threadIdx.x];
+    if (threadIdx.x != 0) return;
+    a.jobs[a.slot] = a.J;
+    a.tlas[a.slot] = a.T;
+    const uint32_t n = a.J.width * a.J.height;
+    if (a.first) start_counters(a.stat, a.counts, n);
+    else a.counts[4] = atomicAdd(a.counts + a.queue, n);
 }
 
-// One camera ray per pixel of frame `slot`, at *base + pixel.
+__global__ void k_start(unsigned long long *stat, uint32_t *counts) {
+    if (threadIdx.x == 0) start_counters(stat, counts, 0u);
+}
+
+// One camera ray per pixel of frame `slot`, at *base + pixel, and the pixel's
+// accumulators cleared.
 __global__ void __launch_bounds__(kT) k_camera_job(RgJobDev J, uint32_t slot, RgQueue q, const uint32_t *base,
-                                                   int64_t cap) {
+                                                   int64_t cap, unsigned long long *acc) {
     int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x;
     const int64_t n = (int64_t)J.width * J.height;
+    if (i >= n) return;
+    accum_clear(acc, (uint64_t)J.pix_off + (uint64_t)i);
     const int64_t at = (int64_t)*base + i;
-    if (i >= n || at >= cap) return;
+    if (at >= cap) return;
     CamF k = camera_basis(J.cam);
     float d[3];
     camera_dir(k, (int)J.width, (int)J.height, i, d);
@@ -466,6 +494,8 @@ struct AoArgs {
     uint32_t *src;
     uint32_t *count;
     uint32_t *block_off;            // per-block offsets (scanned)
+    float *image;                   // nullable: a pixel whose ray missed is 1
+    unsigned long long *stat;       // nullable: stat[1] = the rays emitted
     bool map;
 };
 
@@ -484,11 +514,17 @@ __global__ void k_ao_count(AoArgs a) {
     }
 }
 
-__global__ void k_ao_emit(AoArgs a, int nblocks, const uint32_t *block_cnt_last) {
+// Eight rays per hit pixel, in pixel order.  Each thread takes one pixel's hit
+// geometry (into LDS, hits only), then the block's threads take its rays in
+// order, so that a wave stores 64 consecutive floats per array.  A thread
+// that writes the eight rays of its own pixel stores every eighth float: 9.5M
+// rays 286 us (1.2 TB/s) that way, 130 us this way.
+__global__ void __launch_bounds__(kT) k_ao_emit(AoArgs a, int nblocks) {
     int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x;
     bool h = ao_hit(a, i);
     uint64_t b = __ballot(h);
-    __shared__ uint32_t wc[kT / 64];
+    __shared__ uint32_t wc[kT / 64], px[kT];
+    __shared__ float org[3][kT], nrm[3][kT];
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) wc[w] = (uint32_t)__popcll(b);
     __syncthreads();
@@ -499,45 +535,61 @@ __global__ void k_ao_emit(AoArgs a, int nblocks, const uint32_t *block_cnt_last)
     }
     uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     before += (uint32_t)__popcll(b & lt);
-    uint32_t base = a.block_off[blockIdx.x];
-    if (blockIdx.x == (unsigned)(nblocks - 1) && threadIdx.x == 0) *a.count = base + 8u * tot;
-    if (!h) return;
-    uint32_t rec = a.hit_a[i], slot = a.hit_b[i];
-    if (a.map) {
-        rec = a.rec_of[rec];
-        const RgBlasHdr *hd = reinterpret_cast<const RgBlasHdr *>(a.recs[rec].hdr);
-        slot = reinterpret_cast<const uint32_t *>(hd->slots)[slot];
+    const uint32_t base = a.block_off[blockIdx.x];
+    if (blockIdx.x == (unsigned)(nblocks - 1) && threadIdx.x == 0) {
+        *a.count = base + 8u * tot;
+        if (a.stat) a.stat[1] = base + 8u * tot;
     }
-    float o[3] = {a.ray[0][i], a.ray[1][i], a.ray[2][i]};
-    float d[3] = {a.ray[3][i], a.ray[4][i], a.ray[5][i]};
-    HitGeom g;
-    hit_geometry(a.recs, rec, slot, o, d, a.hit_t[i], g);
-    float eps = offset_eps(g.p);
-    float org[3] = {g.p[0] + eps * g.nf[0], g.p[1] + eps * g.nf[1], g.p[2] + eps * g.nf[2]};
-    uint32_t j0 = base + 8u * before;
-    for (int k = 0; k < 8; ++k) {
+    if (h) {
+        uint32_t rec = a.hit_a[i], slot = a.hit_b[i];
+        if (a.map) {
+            rec = a.rec_of[rec];
+            const RgBlasHdr *hd = reinterpret_cast<const RgBlasHdr *>(a.recs[rec].hdr);
+            slot = reinterpret_cast<const uint32_t *>(hd->slots)[slot];
+        }
+        float o[3] = {a.ray[0][i], a.ray[1][i], a.ray[2][i]};
+        float d[3] = {a.ray[3][i], a.ray[4][i], a.ray[5][i]};
+        HitGeom g;
+        hit_geometry(a.recs, rec, slot, o, d, a.hit_t[i], g);
+        float eps = offset_eps(g.p);
+        for (int q = 0; q < 3; ++q) {
+            org[q][before] = g.p[q] + eps * g.nf[q];
+            nrm[q][before] = g.nf[q];
+        }
+        px[before] = (uint32_t)i;
+    } else if (a.image && i < a.n) {
+        for (int q = 0; q < 3; ++q) a.image[3 * i + q] = 1.0f;
+    }
+    __syncthreads();
+    for (uint32_t r = threadIdx.x; r < 8u * tot; r += kT) {
+        const uint32_t at = r >> 3;
+        const float n_[3] = {nrm[0][at], nrm[1][at], nrm[2][at]}, o_[3] = {org[0][at], org[1][at], org[2][at]};
+        const uint32_t key = px[at] * 8u + (r & 7u);
         float dir[3];
-        ao_dir(g.nf, a.seed, (uint64_t)i * 8ull + (uint64_t)k, dir);
-        put_ray(a.out, j0 + k, org, dir, 0.0f, a.tmax);
-        a.src[j0 + k] = (uint32_t)(i * 8 + k);
+        ao_dir(n_, a.seed, (uint64_t)key, dir);
+        put_ray(a.out, base + r, o_, dir, 0.0f, a.tmax);
+        a.src[base + r] = key;
     }
 }
 
-__global__ void k_ao_accum(const uint8_t *occ, const uint32_t *src, const uint32_t *count,
-                           unsigned long long *acc) {
-    int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j >= (int64_t)*count) return;
-    if (occ[j]) atomicAdd(acc + 3 * (uint64_t)(src[j] >> 3), 1ull);
+// A hit pixel's value from its eight rays, which are consecutive: one minus
+// the share that are occluded (the occlusion bytes are 0 or 1).
+__global__ void __launch_bounds__(kT) k_ao_resolve(const uint8_t *occ, const uint32_t *src, const uint32_t *count,
+                                                   float *image) {
+    const int64_t g = blockIdx.x * (int64_t)kT + threadIdx.x;
+    if (8 * g >= (int64_t)*count) return;
+    const uint64_t o = reinterpret_cast<const uint64_t *>(occ)[g];
+    const float v = 1.0f - (float)__popcll(o) * 0.125f;
+    const uint64_t p = src[8 * g] >> 3;
+    for (int q = 0; q < 3; ++q) image[3 * p + q] = v;
 }
 
-__global__ void k_ao_resolve(const unsigned long long *acc, const uint32_t *hit_rec, int64_t n, float *image) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float v = 1.0f;
-    if (hit_rec[i] != RG_MISS) v = 1.0f - (float)acc[3 * i] * 0.125f;
-    image[3 * i] = v;
-    image[3 * i + 1] = v;
-    image[3 * i + 2] = v;
+// Camera rays of an ambient-occlusion frame, its counters cleared on the way.
+__global__ void __launch_bounds__(kT) k_ao_begin(rg_camera cam, int W, int H, CamRays r, unsigned long long *stat,
+                                                 uint32_t *counts) {
+    const int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x;
+    if (i == 0) start_counters(stat, counts, 0u);
+    if (i < (int64_t)W * H) camera_ray(cam, W, H, i, r);
 }
 
 rg_status ao_generate(AoArgs a, hipStream_t st) {
@@ -546,7 +598,7 @@ rg_status ao_generate(AoArgs a, hipStream_t st) {
     RG_LAUNCH_CHECK();
     rg_status r = rg_scan_excl_u32(a.block_off, nb, st);
     if (r != RG_OK) return r;
-    k_ao_emit<<<nb, kT, 0, st>>>(a, nb, nullptr);
+    k_ao_emit<<<nb, kT, 0, st>>>(a, nb);
     RG_LAUNCH_CHECK();
     return RG_OK;
 }
@@ -554,7 +606,7 @@ rg_status ao_generate(AoArgs a, hipStream_t st) {
 // ------------------------------------------------------ scratch layout
 // ambient occlusion (one frame)
 struct AoBufs {
-    unsigned long long *acc, *stat;
+    unsigned long long *stat;
     uint32_t *counts;
     float *hit_t;
     uint32_t *hit_rec, *hit_slot;
@@ -565,7 +617,7 @@ struct AoBufs {
 };
 
 bool carve_ao(RgArena &A, int64_t n, AoBufs &b) {
-    b.acc = A.take<unsigned long long>(3 * n);
+    A.take<unsigned long long>(3 * n);  // (kept in the size callers have been told)
     b.stat = A.take<unsigned long long>(4);
     b.counts = A.take<uint32_t>(8);
     b.hit_t = A.take<float>(n);
@@ -630,10 +682,8 @@ rg_status run_batch(const rg_batch *B, hipStream_t st) {
     RgWaveBufs b;
     if (!rg_wave_carve(A, B->total_pixels, B->capacity, B->n_jobs, B->n_mats, b)) return RG_ERR_OUT_OF_MEMORY;
     const int64_t total = B->total_pixels;
-    k_zero_u64<<<rg_blocks(3 * total, kT), kT, 0, st>>>(b.acc, 3 * total);
-    rg_status r = rg_wave_reset(b, st);
-    if (r != RG_OK) return r;
-    k_camera_batch<<<rg_blocks(total, kT), kT, 0, st>>>(b.jobs, B->n_jobs, total, b.q[0], b.counts + 0);
+    rg_status r = RG_OK;
+    k_camera_batch<<<rg_blocks(total, kT), kT, 0, st>>>(b.jobs, B->n_jobs, total, b.q[0], b.acc, b.stat, b.counts);
     RG_LAUNCH_CHECK();
     for (int k = 0; k <= B->max_depth; ++k) {
         r = rg_wave_pass(b, B->width, k, B->cap_at[k], st, RG_TUNE_FRAME, B->has_inst_flags != 0);
@@ -750,31 +800,36 @@ bool rg_wave_carve(RgArena &A, int64_t pixels, int64_t cap, int64_t n_jobs, int6
 }
 
 rg_status rg_wave_reset(const RgWaveBufs &b, hipStream_t st) {
-    k_zero_u64<<<1, kT, 0, st>>>(b.stat, 4);
-    k_fill_u32<<<1, kT, 0, st>>>(b.counts, 0u, 8);
+    k_start<<<1, 64, 0, st>>>(b.stat, b.counts);
     RG_LAUNCH_CHECK();
     return RG_OK;
 }
 
-rg_status rg_wave_put_job(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, const RgTlasRef &T,
-                          const rg_material *host_mats, int32_t n_mats, hipStream_t st) {
-    k_put_job<<<1, 64, 0, st>>>(b.jobs, b.tlas, slot, J, T);
-    for (int32_t c = 0; c < n_mats; c += kMatChunk) {
+rg_status rg_wave_put_frame(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, const RgTlasRef &T,
+                            const rg_material *host_mats, int32_t n_mats, bool first, int queue, hipStream_t st) {
+    PutFrame p;
+    p.jobs = b.jobs;
+    p.tlas = b.tlas;
+    p.mats = b.mats + J.mat_off;
+    p.stat = b.stat;
+    p.counts = b.counts;
+    p.J = J;
+    p.T = T;
+    p.slot = slot;
+    p.queue = queue & 1;
+    p.first = first;
+    p.n_mats = n_mats < kMatChunk ? n_mats : kMatChunk;
+    memcpy(p.m.m, host_mats, sizeof(RgMat) * (size_t)p.n_mats);
+    k_put_frame<<<1, kMatChunk, 0, st>>>(p);
+    for (int32_t c = kMatChunk; c < n_mats; c += kMatChunk) {
         MatChunk m;
         const int cnt = n_mats - c < kMatChunk ? n_mats - c : kMatChunk;
         memcpy(m.m, host_mats + c, sizeof(RgMat) * (size_t)cnt);
         k_put_mats<<<1, kMatChunk, 0, st>>>(b.mats + J.mat_off + c, m, cnt);
     }
-    const int64_t n = 3 * (int64_t)J.width * J.height;
-    k_zero_u64<<<rg_blocks(n, kT), kT, 0, st>>>(b.acc + 3 * (uint64_t)J.pix_off, n);
-    RG_LAUNCH_CHECK();
-    return RG_OK;
-}
-
-rg_status rg_wave_camera(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, int queue, hipStream_t st) {
+    // counts[4] holds the frame's first entry (zero for the first frame)
     const int64_t n = (int64_t)J.width * J.height;
-    k_reserve<<<1, 64, 0, st>>>(b.counts + (queue & 1), (uint32_t)n, b.counts + 4);
-    k_camera_job<<<rg_blocks(n, kT), kT, 0, st>>>(J, slot, b.q[queue & 1], b.counts + 4, b.cap);
+    k_camera_job<<<rg_blocks(n, kT), kT, 0, st>>>(J, slot, b.q[queue & 1], b.counts + 4, b.cap, b.acc);
     RG_LAUNCH_CHECK();
     return RG_OK;
 }
@@ -784,7 +839,8 @@ rg_status rg_wave_pass(const RgWaveBufs &b, int32_t width, int64_t pass, int64_t
     if (bound < 1) return RG_OK;
     if (bound > b.cap) bound = b.cap;
     const RgQueue &qin = b.q[pass & 1], &qout = b.q[(pass + 1) & 1];
-    uint32_t *cin = b.counts + (pass & 1), *cout = b.counts + ((pass + 1) & 1), *csq = b.counts + 2;
+    uint32_t *cin = b.counts + (pass & 1), *cout = b.counts + ((pass + 1) & 1);
+    uint32_t *csq = b.counts + 2 + (pass & 1);
     RgTraceArgs tc = {};
     for (int c = 0; c < 8; ++c) tc.ray[c] = qin.ray[c];
     tc.n = bound;
@@ -797,10 +853,9 @@ rg_status rg_wave_pass(const RgWaveBufs &b, int32_t width, int64_t pass, int64_t
     tc.opt = opt;
     rg_status r = rg_trace_launch(width, false, rgt::kRender, tc, st, scope);
     if (r != RG_OK) return r;
-    // the shadow queue and its count are reused below: the previous pass's
-    // shadow work must be done with them
+    // the shadow queue is reused below, and the previous pass's shadow work
+    // empties the queues that shading appends to: it must be done
     if (side && side->pending) RG_HIP(hipStreamWaitEvent(st, side->shadowed, 0));
-    k_pass_counts<<<1, 1, 0, st>>>(b.stat, cin, cout, csq);
     ShadeArgs sa;
     sa.in = qin;
     sa.count_in = cin;
@@ -841,8 +896,12 @@ rg_status rg_wave_pass(const RgWaveBufs &b, int32_t width, int64_t pass, int64_t
     ts.opt = opt;
     r = rg_trace_launch(width, true, rgt::kRender, ts, s2, scope);
     if (r != RG_OK) return r;
-    k_stat_add<<<1, 1, 0, s2>>>(b.stat + 1, csq);
-    k_shadow_resolve<<<rg_blocks(bound, kT), kT, 0, s2>>>(b.sq, csq, b.acc);
+    {
+        const int64_t want = (int64_t)rg_cu_count() * 8;
+        const int64_t need = rg_blocks(bound, kT);
+        k_shadow_resolve<<<(unsigned)(need < want ? need : want), kT, 0, s2>>>(b.sq, b.counts, pass, bound, b.acc,
+                                                                              b.stat);
+    }
     RG_LAUNCH_CHECK();
     if (side) {
         RG_HIP(hipEventRecord(side->shadowed, s2));
@@ -865,8 +924,9 @@ rg_status rg_camera_rays(const rg_camera *cam, int32_t width, int32_t height, fl
     for (int k = 0; k < 8; ++k)
         if (!rays[k]) return RG_ERR_INVALID_ARG;
     int64_t n = (int64_t)width * height;
-    k_camera_rays<<<rg_blocks(n, kT), kT, 0, (hipStream_t)stream>>>(
-        *cam, width, height, rays[0], rays[1], rays[2], rays[3], rays[4], rays[5], rays[6], rays[7]);
+    CamRays cr;
+    for (int k = 0; k < 8; ++k) cr.a[k] = rays[k];
+    k_camera_rays<<<rg_blocks(n, kT), kT, 0, (hipStream_t)stream>>>(*cam, width, height, cr);
     RG_LAUNCH_CHECK();
     return rg_debug_done(RG_OK, (hipStream_t)stream);
 }
@@ -1084,9 +1144,7 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
         J.gbuf = primary_mat;
         RgTlasRef T = {(const char *)tlas->buf + tlas->nodes_off,
                        (const RgInst *)((const char *)tlas->buf + tlas->inst_off)};
-        if ((r = rg_wave_reset(b, st)) != RG_OK) return r;
-        if ((r = rg_wave_put_job(b, 0, J, T, mats, n_mats, st)) != RG_OK) return r;
-        if ((r = rg_wave_camera(b, 0, J, 0, st)) != RG_OK) return r;
+        if ((r = rg_wave_put_frame(b, 0, J, T, mats, n_mats, true, 0, st)) != RG_OK) return r;
         for (int k = 0; k <= max_depth; ++k) {
             if ((r = rg_wave_pass(b, tlas->width, k, n << k, st, RG_TUNE_FRAME, tlas->has_inst_flags != 0)) != RG_OK)
                 return r;
@@ -1097,9 +1155,9 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
                 ca.hit_t = b.hit_t;
                 ca.hit_rec = b.hit_rec;
                 ca.hit_slot = b.hit_slot;
-                ca.ccount = b.counts + (k & 1);
+                ca.ccount = b.counts + 5;
                 ca.sq = b.sq;
-                ca.scount = b.counts + 2;
+                ca.scount = b.counts + 6;
                 ca.T = T;
                 ca.cap = capture->capacity;
                 ca.k = k;
@@ -1122,11 +1180,9 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
         const rg_status re = ev.start(st);
         if (re != RG_OK) return re;
     }
-    k_zero_u64<<<rg_blocks(3 * n, kT), kT, 0, st>>>(b.acc, 3 * n);
-    k_zero_u64<<<1, kT, 0, st>>>(b.stat, 4);
-    k_fill_u32<<<1, kT, 0, st>>>(b.counts, 0u, 8);
-    k_camera_rays<<<rg_blocks(n, kT), kT, 0, st>>>(*cam, width, height, b.cam[0], b.cam[1], b.cam[2], b.cam[3],
-                                                   b.cam[4], b.cam[5], b.cam[6], b.cam[7]);
+    CamRays cr;
+    for (int c = 0; c < 8; ++c) cr.a[c] = b.cam[c];
+    k_ao_begin<<<rg_blocks(n, kT), kT, 0, st>>>(*cam, width, height, cr, b.stat, b.counts);
     RG_LAUNCH_CHECK();
     RgTraceArgs ta = trace_args(tlas);
     for (int c = 0; c < 8; ++c) ta.ray[c] = b.cam[c];
@@ -1149,6 +1205,8 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
     a.src = b.ao_src;
     a.count = b.counts + 2;
     a.block_off = b.ao_blk;
+    a.image = image;
+    a.stat = b.stat;
     a.map = false;
     r = ao_generate(a, st);
     if (r != RG_OK) return r;
@@ -1159,11 +1217,8 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
     tb.occluded = b.ao_occ;
     r = rg_trace_launch(tlas->width, true, rgt::kRender, tb, st, RG_TUNE_FRAME);
     if (r != RG_OK) return r;
-    k_ao_accum<<<rg_blocks(8 * n, kT), kT, 0, st>>>(b.ao_occ, b.ao_src, b.counts + 2, b.acc);
-    k_ao_resolve<<<rg_blocks(n, kT), kT, 0, st>>>(b.acc, b.hit_rec, n, image);
+    k_ao_resolve<<<rg_blocks(n, kT), kT, 0, st>>>(b.ao_occ, b.ao_src, b.counts + 2, image);
     RG_LAUNCH_CHECK();
-    k_stat_add<<<1, 1, 0, st>>>(b.stat, b.counts + 0);
-    k_stat_add<<<1, 1, 0, st>>>(b.stat + 1, b.counts + 2);
     if (stats) return finish_stats(st, ev.e0, ev.e1, b.stat, stats);
     return RG_OK;
 }

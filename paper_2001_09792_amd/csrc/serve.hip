@@ -338,8 +338,7 @@ rg_status rg_engine_admit(rg_engine *E, const rg_job *J, int64_t tag, int32_t *a
     D.start = E->pass;
     D.image = J->image;
     RgTlasRef T = {(const char *)t->buf + t->nodes_off, (const RgInst *)((const char *)t->buf + t->inst_off)};
-    r = rg_wave_put_job(E->b, (uint32_t)slot, D, T, J->mats, J->n_mats, E->st);
-    if (r == RG_OK) r = rg_wave_camera(E->b, (uint32_t)slot, D, (int)(E->pass & 1), E->st);
+    r = rg_wave_put_frame(E->b, (uint32_t)slot, D, T, J->mats, J->n_mats, false, (int)(E->pass & 1), E->st);
     if (r != RG_OK) {
         pool_release(E->pool, slot);
         return r;

@@ -39,8 +39,10 @@ struct RgJobDev {
 };
 
 // Device buffers of a wavefront render, carved from one caller buffer:
-// accumulators (3 x u64 per pixel), statistics, queue counters (0, 1: the
-// two ray queues, 2: the shadow queue), frame / top-level / material tables,
+// accumulators (3 x u64 per pixel), statistics, counters (0, 1: entries of the
+// two ray queues; 2, 3: of the shadow queue in passes of either parity; 4: the
+// first entry reserved for a frame's camera rays; 5, 6: rays and shadow rays
+// of the last pass), frame / top-level / material tables,
 // hit arrays, two ray queues and a shadow queue of `cap` entries each.
 struct RgWaveBufs {
     unsigned long long *acc, *stat;
@@ -59,18 +61,18 @@ struct RgWaveBufs {
 // the arena is too small.
 bool rg_wave_carve(RgArena &A, int64_t pixels, int64_t cap, int64_t n_jobs, int64_t n_mats, RgWaveBufs &b);
 
-// Zeroes the statistics and the three queue counters.
+// Zeroes the statistics and the queue counters.
 rg_status rg_wave_reset(const RgWaveBufs &b, hipStream_t st);
 
 // Writes frame record `slot` (and its top-level reference) and n_mats
 // materials at b.mats + J.mat_off, through kernel arguments, so the host
 // arrays may go away when this returns and nothing waits; zeroes the
-// frame's accumulators.
-rg_status rg_wave_put_job(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, const RgTlasRef &T,
-                          const rg_material *host_mats, int32_t n_mats, hipStream_t st);
-
-// Appends the frame's camera rays (one per pixel) to ray queue `queue`.
-rg_status rg_wave_camera(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, int queue, hipStream_t st);
+// frame's accumulators and appends its camera rays (one per pixel) to ray
+// queue `queue`.  Two launches (and one per 64 materials beyond the first
+// 64).  first: the only frame of a render; the statistics and the counters
+// start over with its rays (no rg_wave_reset needed).
+rg_status rg_wave_put_frame(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, const RgTlasRef &T,
+                            const rg_material *host_mats, int32_t n_mats, bool first, int queue, hipStream_t st);
 
 // A second stream for the shadow half of each pass.  The shadow rays of
 // pass p are traced and their direct term added on `st` while the main
