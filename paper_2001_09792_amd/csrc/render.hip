@@ -1214,6 +1214,7 @@ static rg_status render_impl(const rg_tlas *tlas, const rg_material *mats, int32
     for (int c = 0; c < 8; ++c) tb.ray[c] = b.ao_ray[c];
     tb.n = 8 * n;
     tb.count = b.counts + 2;
+    tb.lanes = true;  // eight rays for every hit pixel
     tb.occluded = b.ao_occ;
     r = rg_trace_launch(tlas->width, true, rgt::kRender, tb, st, RG_TUNE_FRAME);
     if (r != RG_OK) return r;

@@ -17,6 +17,22 @@ namespace {
 // flight when its slot is needed again (a straggler) is written out as far as
 // it got; its late rays then store their results directly.
 constexpr int kStageSlots = 4;
+// What a kernel variant holds: the persistent traversal with a ray per lane,
+// the one with a group of lanes per ray (trace_groups), or both, the kernel
+// choosing by the number of rays it finds.  A launch of up to kGroupRays rays
+// per resident group takes groups (two-level scene, width 4, random rays, a
+// lane per ray / groups at 1, 2, 3 rays per group: 1,000 rays 46.7 / 38.1 /
+// 37.3 / 37.5 us, 16,384 rays 84.6 / 66.2 / 65.4 / 65.4, 100,000 rays 99.7 /
+// 100.2 / 91.8 / 92.1; a 256x256 frame 182 / 139 / 138 / 138, a 1080p depth-4
+// frame at width 8 1,468 / 1,383 / 1,374 / 1,414).  A launch whose size the
+// host knows gets the variant it needs; a pass of a frame, whose size only
+// the device knows, the one with both.  That one holds 109 registers where
+// the plain one holds 95 (width 4), so the launches that are always long (the
+// occlusion rays of a frame) and the engine's, which share the chip with the
+// launches of another stream and lose by groups (11.98 -> 12.56 ms for 24
+// requests), take the plain one.
+enum Path { kLanes = 0, kGroups = 1, kEither = 2 };
+constexpr uint32_t kGroupRays = 2;
 constexpr uint32_t kClaimMin = 16;  // packets per wave from which a launch claims its last quarter
 template <bool ANY, int MODE>
 struct StageShape {
@@ -66,8 +82,8 @@ __device__ inline uint64_t uniform64(uint64_t v) {
 // start and at the end costs more than the imbalance it removes, and every
 // packet goes out interleaved.  In a launch with fewer than 64 rays per wave
 // each wave takes one packet of fewer rays.
-template <int W, bool ANY, int MODE, bool OPT>
-__global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refill, int lds_depth, int leaf_batch,
+template <int W, bool ANY, int MODE, bool OPT, int PATH>
+__global__ void __launch_bounds__(rgt::kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_trace(RgTraceArgs a, int refill, int lds_depth, int leaf_batch,
                                                          int inst_batch) {
     constexpr int K = StageShape<ANY, MODE>::K;
     extern __shared__ uint32_t lds_stack[];  // lds_depth * kThreads stack entries, then the staging rings
@@ -168,6 +184,35 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
         a.counts[3 * i + 1] = tr.h.n_tris;
         a.counts[3 * i + 2] = tr.h.n_inst;
     };
+    // Starts this lane on ray idx; false if it has nothing to do.
+    auto take_ray = [&](uint32_t idx) -> bool {
+        rgt::Ray R;
+        R.o[0] = a.ray[0][idx]; R.o[1] = a.ray[1][idx]; R.o[2] = a.ray[2][idx];
+        R.d[0] = a.ray[3][idx]; R.d[1] = a.ray[4][idx]; R.d[2] = a.ray[5][idx];
+        R.tmin = a.ray[6][idx];
+        R.tmax = a.ray[7][idx];
+        if (MODE == rgt::kRender && a.ray_job) {  // only frames carry per-ray top levels
+            const RgTlasRef J = a.jobs[a.ray_job[idx]];
+            tr.tlas_nodes = reinterpret_cast<const RgNode<W> *>(J.nodes);
+            tr.recs = J.recs;
+        }
+        const bool live = tr.begin(R);
+        if (OPT) tr.rmask = a.ray_mask ? (uint32_t)a.ray_mask[idx] : a.mask;
+        return live;
+    };
+    if constexpr (PATH != kLanes) {
+        if (PATH == kGroups || n <= n_waves * (64u / W) * kGroupRays) {
+            // group stacks overlay the lane stacks and the staging rings
+            rgt::trace_groups(tr, wave * per_wave, min(n, (wave + 1u) * per_wave),
+                              (uint32_t RG_LDS *)lds_stack + wib * (64u / W) * rgt::kStackCap, take_ray,
+                              [&](uint32_t i) {
+#pragma unroll
+                                  for (int w = 0; w < K; ++w) store(w, i, word(w));
+                              });
+            return;
+        }
+    }
+    if constexpr (PATH == kGroups) return;
     // Writes slot s's staged rays, those of launch packet pkt (all lanes
     // together; uniform arguments).
     auto flush_slot = [&](int s, uint32_t pkt, uint64_t m) {
@@ -281,20 +326,9 @@ __global__ void __launch_bounds__(rgt::kThreads) k_trace(RgTraceArgs a, int refi
                 const uint32_t idx = (pkt << psh) + (j & 63);
                 if (pkt < n_packets && (j & 63) < psize && idx < n) {
                     if (K == 0 && rgt::lane_in(m_pend)) write_result();
-                    rgt::Ray R;
-                    R.o[0] = a.ray[0][idx]; R.o[1] = a.ray[1][idx]; R.o[2] = a.ray[2][idx];
-                    R.d[0] = a.ray[3][idx]; R.d[1] = a.ray[4][idx]; R.d[2] = a.ray[5][idx];
-                    R.tmin = a.ray[6][idx];
-                    R.tmax = a.ray[7][idx];
                     ray_j = j;
                     ray_i = idx;
-                    if (MODE == rgt::kRender && a.ray_job) {  // only frames carry per-ray top levels
-                        const RgTlasRef J = a.jobs[a.ray_job[idx]];
-                        tr.tlas_nodes = reinterpret_cast<const RgNode<W> *>(J.nodes);
-                        tr.recs = J.recs;
-                    }
-                    live = tr.begin(R);
-                    if (OPT) tr.rmask = a.ray_mask ? (uint32_t)a.ray_mask[idx] : a.mask;
+                    live = take_ray(idx);
                     took = true;
                 }
             }
@@ -420,12 +454,12 @@ __global__ void __launch_bounds__(256) k_refine(RefineArgs a) {
 // / 6.70 with refill 16, 6.55 / 6.09 / 6.47 with refill 24 (which costs 2.2M
 // any-hit rays 1.5%); without waiting lanes (batching 1 / 1) 6.70 / 6.45 / 6.80.  A served stream of 24 requests
 // at 12 / 16 / 20 waves: 12.6 / 12.3 / 12.7 ms.  Frames, coherent at first,
-// are within 2% of each other from 16 to 24 waves and refill 8 to 24; lanes
-// waiting at leaves for 12 others cost them up to 60%, for 4 others they gain
-// 1-2% (24 frames 1.82 -> 1.79 ms, 1080p depth-4 frame 1.59 -> 1.57 ms).
+// are within 2% of each other from 16 to 24 waves and refill 8 to 24 (24
+// frames 1.82 -> 1.80 ms from 16 / 8 to 20 / 16); lanes waiting at leaves for
+// 12 others cost them up to 60%.
 rg_trace_tune g_tune[RG_TUNE_SCOPES] = {
     {16, 16, 16, 12, 6},  // RG_TUNE_TRACE: rg_trace_closest / any / counts
-    {16, 20, 16, 4, 2},   // RG_TUNE_FRAME: rg_render, rg_batch_render
+    {16, 20, 16, 1, 1},   // RG_TUNE_FRAME: rg_render, rg_batch_render
     {24, 16, 16, 12, 6},  // RG_TUNE_ENGINE: rg_engine_step
 };
 
@@ -469,11 +503,29 @@ unsigned resident_cap(Kernel kernel, unsigned blocks, size_t shm) {
     return blocks < cap ? blocks : cap;
 }
 
-template <int W, bool ANY, int MODE, bool OPT>
-void launch_one(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
-    auto kernel = k_trace<W, ANY, MODE, OPT>;
+template <int W, bool ANY, int MODE, bool OPT, int PATH>
+void launch_path(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
+    auto kernel = k_trace<W, ANY, MODE, OPT, PATH>;
+    if (PATH != kLanes) {
+        const size_t groups = (size_t)(rgt::kThreads / W) * rgt::kStackCap * sizeof(uint32_t);
+        shm = PATH == kGroups || shm < groups ? groups : shm;
+    }
     blocks = resident_cap(kernel, blocks, shm);
     kernel<<<blocks, rgt::kThreads, shm, st>>>(a, t.refill, t.lds_depth, t.leaf_batch, t.inst_batch);
+}
+
+template <int W, bool ANY, int MODE, bool OPT>
+void launch_one(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
+    if constexpr (W >= 4 && MODE != rgt::kCounts) {
+        if (!a.lanes) {
+            const int64_t small = (int64_t)blocks * rgt::kThreads / W * kGroupRays;
+            if (a.n <= small) return launch_path<W, ANY, MODE, OPT, kGroups>(a, st, blocks, shm, t);
+            if constexpr (MODE == rgt::kRender) {
+                if (a.count) return launch_path<W, ANY, MODE, OPT, kEither>(a, st, blocks, shm, t);
+            }
+        }
+    }
+    launch_path<W, ANY, MODE, OPT, kLanes>(a, st, blocks, shm, t);
 }
 
 template <int W, bool OPT>
@@ -614,6 +666,7 @@ rg_status rg_trace_launch(int width, bool any, int mode, const RgTraceArgs &a_in
     if (width != 2 && width != 4 && width != 8) return RG_ERR_INVALID_ARG;
     const rg_trace_tune t = g_tune[scope];
     RgTraceArgs a = a_in;
+    a.lanes = a.lanes || scope == RG_TUNE_ENGINE;
     rg_status r = work_counter(st, &a.work);
     if (r != RG_OK) return r;
     if (width == 2) return rg_debug_done(launch_w<2>(any, mode, a, st, t), st);

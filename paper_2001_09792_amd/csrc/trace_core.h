@@ -310,43 +310,51 @@ struct Tracer {
         return R.tmin <= R.tmax;
     }
 
+    // Slab distances as one fused plane * inv - c each.  The constant
+    // c of the lo planes and that of the hi planes sit on either side
+    // of o * inv, kSlabShift |o| |inv| apart from it, on the side that
+    // widens the slab whatever the sign of inv, so the rounding of
+    // o * inv cannot narrow an interval; the far widening covers the
+    // relative error as before.
+    __device__ inline void slab_consts(float cl[3], float chh[3]) const {
+        const float o_[3] = {ox, oy, oz}, i_[3] = {ix, iy, iz};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float c = o_[a] * i_[a], sh_ = kSlabShift * fabsf(o_[a]);
+            cl[a] = fmaf(sh_, i_[a], c);
+            chh[a] = fmaf(-sh_, i_[a], c);
+        }
+    }
+    // Entry distance of a child box in the frame's interval, INFINITY if
+    // the ray misses it or the slot is empty.
+    __device__ inline float slab(const float lo[3], const float hi[3], const float cl[3], const float chh[3],
+                                 uint32_t child) const {
+        const float x0 = fmaf(lo[0], ix, -cl[0]), x1 = fmaf(hi[0], ix, -chh[0]);
+        const float y0 = fmaf(lo[1], iy, -cl[1]), y1 = fmaf(hi[1], iy, -chh[1]);
+        const float z0 = fmaf(lo[2], iz, -cl[2]), z1 = fmaf(hi[2], iz, -chh[2]);
+        const float n_ = fmaxf(fmaxf(fminf(x0, x1), fminf(y0, y1)), fmaxf(fminf(z0, z1), tlo));
+        float f_ = fminf(fminf(fmaxf(x0, x1), fmaxf(y0, y1)), fmaxf(z0, z1));
+        f_ = fmaf(fabsf(f_), kFarWiden, f_);
+        f_ = fminf(f_, thi);
+        const bool hit = (n_ <= f_) & (child != RG_EMPTY);
+        return hit ? n_ : INFINITY;
+    }
+
     // An inner node: tests its children, continues with the nearest hit one
     // and pushes the others far first; cur = RG_EMPTY if none is hit.
     __device__ inline void inner(const uint32_t *w, bool shallow) {
         if (MODE == kCounts) ++h.n_nodes;
         float tn[W];
         uint32_t ch[W];
-        // slab distances as one fused plane * inv - c each.  The constant
-        // c of the lo planes and that of the hi planes sit on either side
-        // of o * inv, kSlabShift |o| |inv| apart from it, on the side that
-        // widens the slab whatever the sign of inv, so the rounding of
-        // o * inv cannot narrow an interval; the far widening covers the
-        // relative error as before
         float cl[3], chh[3];
-        {
-            const float o_[3] = {ox, oy, oz}, i_[3] = {ix, iy, iz};
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float c = o_[a] * i_[a], sh_ = kSlabShift * fabsf(o_[a]);
-                cl[a] = fmaf(sh_, i_[a], c);
-                chh[a] = fmaf(-sh_, i_[a], c);
-            }
-        }
+        slab_consts(cl, chh);
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            const float lx = __uint_as_float(w[k]), ly = __uint_as_float(w[W + k]);
-            const float lz = __uint_as_float(w[2 * W + k]), hx = __uint_as_float(w[3 * W + k]);
-            const float hy = __uint_as_float(w[4 * W + k]), hz = __uint_as_float(w[5 * W + k]);
-            const float x0 = fmaf(lx, ix, -cl[0]), x1 = fmaf(hx, ix, -chh[0]);
-            const float y0 = fmaf(ly, iy, -cl[1]), y1 = fmaf(hy, iy, -chh[1]);
-            const float z0 = fmaf(lz, iz, -cl[2]), z1 = fmaf(hz, iz, -chh[2]);
-            float n_ = fmaxf(fmaxf(fminf(x0, x1), fminf(y0, y1)), fmaxf(fminf(z0, z1), tlo));
-            float f_ = fminf(fminf(fmaxf(x0, x1), fmaxf(y0, y1)), fmaxf(z0, z1));
-            f_ = fmaf(fabsf(f_), kFarWiden, f_);
-            f_ = fminf(f_, thi);
+            const float lo[3] = {__uint_as_float(w[k]), __uint_as_float(w[W + k]), __uint_as_float(w[2 * W + k])};
+            const float hi[3] = {__uint_as_float(w[3 * W + k]), __uint_as_float(w[4 * W + k]),
+                                 __uint_as_float(w[5 * W + k])};
             ch[k] = w[6 * W + k];
-            const bool hit = (n_ <= f_) & (ch[k] != RG_EMPTY);
-            tn[k] = hit ? n_ : INFINITY;
+            tn[k] = slab(lo, hi, cl, chh, ch[k]);
         }
         if (!ANY) sort_children<W>(tn, ch);
         if (shallow) cur = push<true>(tn, ch);
@@ -375,18 +383,20 @@ struct Tracer {
     // A top-level leaf: one instance.  Record words: inv[9] 0..8, p[3]
     // 9..11, nodes 12..13, tris 14..15, hdr 16..17, mat 18, inst 19,
     // root box lo 20..22, hi 23..25, flags 26.
-    __device__ inline void enter(const uint32_t *w) {
+    // w(i) gives word i.
+    template <class Words>
+    __device__ inline void enter(Words w) {
         if (MODE == kCounts) ++h.n_inst;
         // object-space ray in double: o' = M^-1 (o - p), d' = M^-1 d
-        const double q[3] = {(double)R.o[0] - (double)__uint_as_float(w[9]),
-                             (double)R.o[1] - (double)__uint_as_float(w[10]),
-                             (double)R.o[2] - (double)__uint_as_float(w[11])};
+        const double q[3] = {(double)R.o[0] - (double)__uint_as_float(w(9)),
+                             (double)R.o[1] - (double)__uint_as_float(w(10)),
+                             (double)R.o[2] - (double)__uint_as_float(w(11))};
         const double e[3] = {(double)R.d[0], (double)R.d[1], (double)R.d[2]};
         double od[3], dd[3];
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
-            const double ir0 = __uint_as_float(w[3 * r]), ir1 = __uint_as_float(w[3 * r + 1]);
-            const double ir2 = __uint_as_float(w[3 * r + 2]);
+            const double ir0 = __uint_as_float(w(3 * r)), ir1 = __uint_as_float(w(3 * r + 1));
+            const double ir2 = __uint_as_float(w(3 * r + 2));
             od[r] = fma(ir2, q[2], fma(ir0, q[0], ir1 * q[1]));
             dd[r] = fma(ir2, e[2], fma(ir0, e[0], ir1 * e[1]));
         }
@@ -397,7 +407,7 @@ struct Tracer {
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const float of = (float)od[r], df = (float)dd[r], rr = safe_rcp(df);
-            const float a = (__uint_as_float(w[20 + r]) - of) * rr, b = (__uint_as_float(w[23 + r]) - of) * rr;
+            const float a = (__uint_as_float(w(20 + r)) - of) * rr, b = (__uint_as_float(w(23 + r)) - of) * rr;
             ten = fmaxf(ten, fminf(a, b));
             tex = fminf(tex, fmaxf(a, b));
         }
@@ -416,17 +426,17 @@ struct Tracer {
         tlo = fmaf(fabsf(tlo), -1.2e-7f, tlo);
         thi = best - t0;
         thi = fmaf(fabsf(thi), 2.4e-7f, thi);
-        nodes = (uint64_t)w[12] | ((uint64_t)w[13] << 32);
-        leaves = (uint64_t)w[14] | ((uint64_t)w[15] << 32);
-        inst_id = (MODE == kRender) ? rg_leaf_first(cur) : w[19];
+        nodes = (uint64_t)w(12) | ((uint64_t)w(13) << 32);
+        leaves = (uint64_t)w(14) | ((uint64_t)w(15) << 32);
+        inst_id = (MODE == kRender) ? rg_leaf_first(cur) : w(19);
         if (OPT) {
-            cull = (w[26] & RG_INST_CULL_DISABLE) ? 0u : call_cull;
+            cull = (w(26) & RG_INST_CULL_DISABLE) ? 0u : call_cull;
             // the facing reads the sign of det in the published axis order,
             // which swaps x and y for a direction with d[kz] < 0
-            if (cull) cull ^= (((w[26] & RG_INST_FLIP_FACING) != 0u) != mirrored) ? kFlip : 0u;
+            if (cull) cull ^= (((w(26) & RG_INST_FLIP_FACING) != 0u) != mirrored) ? kFlip : 0u;
             alpha = nullptr;
-            if (w[26] & RG_INST_ALPHA) {
-                const RgBlasHdr *H = reinterpret_cast<const RgBlasHdr *>((uint64_t)w[16] | ((uint64_t)w[17] << 32));
+            if (w(26) & RG_INST_ALPHA) {
+                const RgBlasHdr *H = reinterpret_cast<const RgBlasHdr *>((uint64_t)w(16) | ((uint64_t)w(17) << 32));
                 alpha = reinterpret_cast<const uint64_t *>(H->alpha);
                 alpha_level = H->alpha_level;
             }
@@ -436,7 +446,8 @@ struct Tracer {
     }
 
     // One triangle (ten words: vertices, input index) in leaf slot `slot`.
-    __device__ inline void triangle(const uint32_t *w, uint32_t slot) {
+    // Returns whether it became the hit.
+    __device__ inline bool triangle(const uint32_t *w, uint32_t slot) {
         if (MODE == kCounts) ++h.n_tris;
         const float o3[3] = {ox, oy, oz};
         float tv[9];
@@ -470,6 +481,7 @@ struct Tracer {
                 thi = fmaf(fabsf(thi), 2.4e-7f, thi);
             }
         }
+        return ok;
     }
 
     // One round: inner nodes whenever a lane has one; leaves and instance
@@ -528,7 +540,7 @@ struct Tracer {
         uint64_t hidden = 0ull, stop = 0ull;
         if (m_inst) {
             if (OPT) hidden = ballot(((w[26] & 0xFFu) & rmask) == 0u) & m_inst;  // not visible: as if missed
-            if (lane_in(m_inst & ~hidden)) enter(w);
+            if (lane_in(m_inst & ~hidden)) enter([&](int i) { return w[i]; });
             if (OPT && lane_in(hidden)) cur = RG_EMPTY;
         }
         if (m_leaf) {
@@ -559,6 +571,192 @@ struct Tracer {
     }
 };
 
+// Value of the lane at `ctrl` (DPP: quad_perm, row_half_mirror); every lane
+// read from is active.
+template <int CTRL>
+__device__ inline uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+constexpr int kQuad1 = 0xB1, kQuad2 = 0x4E, kQuad3 = 0x1B;  // quad_perm: lane ^ 1, ^ 2, ^ 3
+constexpr int kHalfMirror = 0x141;                          // lane 7 - i of each eight
+
+// The traversal for short launches: W lanes (a group) per ray, one child box
+// or one triangle of a leaf per lane, 64 / W rays per wave.  A short launch
+// lasts as long as its longest rays, and one ray's time is the latency of the
+// instructions of its rounds: with a lane per ray a round of an inner node is
+// about 260 vector and 90 scalar instructions (1 us; memory is the smaller
+// part: requesting the children's lines early made it 10% slower).  Here the
+// box test is one child's, the order of the children is each lane's rank
+// among the W entry distances (DPP), and a leaf's triangles are tested side by
+// side.  All lanes of a group hold the ray's state alike.  The same units are
+// visited as in Tracer::round; children at equal distances go in slot order.
+template <int W, bool ANY, int MODE, bool OPT, class Fetch, class Put>
+__device__ inline void trace_groups(Tracer<W, ANY, MODE, OPT> &tr, uint32_t first_ray, uint32_t end_ray,
+                                    uint32_t RG_LDS *stacks, Fetch fetch, Put put) {
+    static_assert(W == 4 || W == 8, "group width");
+    constexpr uint32_t G = 64 / W;
+    const uint32_t lane = threadIdx.x & 63u, k = lane & (W - 1u), grp = lane / W;
+    uint32_t RG_LDS *stk = stacks + grp * kStackCap;
+    uint32_t next_ray = first_ray + grp, ray = 0u;
+    uint64_t has = 0ull, blas = 0ull;
+    uint32_t stalled = 0u;
+    while (true) {
+        const uint64_t take = ballot(next_ray < end_ray) & ~has;
+        if (take) {
+            bool live = false;
+            if (lane_in(take)) {
+                ray = next_ray;
+                next_ray += G;
+                live = fetch(ray);
+                if (!live && k == 0u) put(ray);  // empty interval: a miss without traversal
+            }
+            has |= ballot(live);
+            blas &= ~take;
+            stalled = 0u;
+        }
+        if (has == 0ull) {
+            if (ballot(next_ray < end_ray) == 0ull) return;
+            continue;
+        }
+        const uint64_t m_inner = ballot(!rg_is_leaf(tr.cur)) & has;
+        const uint64_t m_leaf = has & ~m_inner & blas, m_inst = has & ~m_inner & ~blas;
+        const uint32_t first = tr.cur & 0x0FFFFFFFu, count = ((tr.cur >> 28) & 7u) + 1u;
+        // every kind's bytes are requested before any is used
+        uint32_t w[10];
+        const uint64_t m_tri = ballot(k < count) & m_leaf;
+        if (lane_in(m_inner)) {
+            const RG_GLOBAL uint32_t *src =
+                gptr<uint32_t>((const void *)(tr.nodes + (uint64_t)first * sizeof(RgNode<W>) + 4u * k));
+#pragma unroll
+            for (int r = 0; r < 7; ++r) w[r] = src[r * W];
+        }
+        if (m_tri && lane_in(m_tri)) {
+            const RG_GLOBAL rg_u2 *src =
+                gptr<rg_u2>((const void *)(tr.leaves + (uint64_t)(first + k) * sizeof(RgTri)));
+#pragma unroll
+            for (int r = 0; r < 5; ++r) {
+                const rg_u2 v = src[r];
+                w[2 * r] = v.x;
+                w[2 * r + 1] = v.y;
+            }
+        }
+        if (m_inst && lane_in(m_inst)) {  // a quarter of the record per lane of a quad
+            const RG_GLOBAL uint32_t *src =
+                gptr<uint32_t>((const void *)(tr.leaves + (uint64_t)first * sizeof(RgInst) + 28u * (k & 3u)));
+#pragma unroll
+            for (int r = 0; r < 7; ++r) w[r] = src[r];
+        }
+        if (lane_in(m_inner)) {
+            const float lo[3] = {__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2])};
+            const float hi[3] = {__uint_as_float(w[3]), __uint_as_float(w[4]), __uint_as_float(w[5])};
+            float cl[3], chh[3];
+            tr.slab_consts(cl, chh);
+            const float tn = tr.slab(lo, hi, cl, chh, w[6]);
+            const bool hit = tn != INFINITY;
+            const uint32_t hits = (uint32_t)(ballot(hit) >> (lane & ~(W - 1u))) & ((1u << W) - 1u);
+            const int nh = __popc(hits);
+            // rank: lanes that come before this one (nearer, or as near and
+            // in a lower slot); any hit goes in slot order
+            uint32_t rank = (uint32_t)__popc(hits & ((1u << k) - 1u));
+            if (!ANY) {
+                rank = 0u;
+                auto before = [&](uint32_t bits, uint32_t other) {
+                    const float t = __uint_as_float(bits);
+                    rank += ((t < tn) | ((t == tn) & (other < k))) ? 1u : 0u;
+                };
+                const uint32_t b = __float_as_uint(tn);
+                before(dpp<kQuad1>(b), k ^ 1u);
+                before(dpp<kQuad2>(b), k ^ 2u);
+                before(dpp<kQuad3>(b), k ^ 3u);
+                if constexpr (W == 8) {
+                    const uint32_t m = dpp<kHalfMirror>(b);
+                    before(m, k ^ 7u);
+                    before(dpp<kQuad1>(m), k ^ 6u);
+                    before(dpp<kQuad2>(m), k ^ 5u);
+                    before(dpp<kQuad3>(m), k ^ 4u);
+                }
+            }
+            // nearest first: it is the next unit, the others lie on the stack
+            // farthest first (any hit: first slot next, the others in order)
+            if (hit & (rank != 0u)) stk[tr.st.sp + (ANY ? (int)rank - 1 : nh - 1 - (int)rank)] = w[6];
+            uint32_t nx = (hit & (rank == 0u)) ? w[6] : 0u;  // no child is node 0
+            nx |= dpp<kQuad1>(nx);
+            nx |= dpp<kQuad2>(nx);
+            if constexpr (W == 8) nx |= dpp<kHalfMirror>(nx);
+            tr.cur = nh ? nx : RG_EMPTY;
+            tr.st.sp += nh ? nh - 1 : 0;
+        }
+        uint64_t hidden = 0ull, stop = 0ull;
+        if (m_inst) {
+            // flags: word 26, the fourth lane's sixth (a mask is only ever set
+            // by all lanes together: under a lane's branch it would differ
+            // from lane to lane)
+            if (OPT) hidden = ballot(((dpp<0xFF>(w[5]) & 0xFFu) & tr.rmask) == 0u) & m_inst;
+            if (lane_in(m_inst & ~hidden)) {
+                tr.enter([&](int i) {
+                    const uint32_t v = w[i % 7];
+                    return i < 7 ? dpp<0x00>(v) : (i < 14 ? dpp<0x55>(v) : (i < 21 ? dpp<0xAA>(v) : dpp<0xFF>(v)));
+                });
+            }
+            if (OPT && lane_in(hidden)) tr.cur = RG_EMPTY;
+        }
+        if (m_leaf) {
+            bool ok = false;
+            if (lane_in(m_tri)) ok = tr.triangle(w, first + k);
+            const uint64_t got = ballot(ok);
+            if (ANY) {
+                // the first of the group's hits
+                stop = ballot(((uint32_t)(got >> (lane & ~(W - 1u))) & ((1u << W) - 1u)) != 0u) & m_leaf;
+                if (lane_in(stop)) {
+                    const uint32_t bits = (uint32_t)(got >> (lane & ~(W - 1u))) & ((1u << W) - 1u);
+                    const int from = (int)(lane & ~(W - 1u)) + __ffs((int)bits) - 1;
+                    tr.h.inst = tr.inst_id;
+                    tr.h.prim = (uint32_t)__shfl((int)tr.h.prim, from);
+                }
+            } else if (got) {
+                // least (t, instance, primitive) over the group
+                if (lane_in(m_leaf)) {
+                    auto least = [&](uint32_t ob, uint32_t oi, uint32_t op) {
+                        const float t = __uint_as_float(ob);
+                        const bool lt = (t < tr.best) |
+                                        ((t == tr.best) & ((oi < tr.h.inst) | ((oi == tr.h.inst) & (op < tr.h.prim))));
+                        tr.best = lt ? t : tr.best;
+                        tr.h.inst = lt ? oi : tr.h.inst;
+                        tr.h.prim = lt ? op : tr.h.prim;
+                    };
+                    least(dpp<kQuad1>(__float_as_uint(tr.best)), dpp<kQuad1>(tr.h.inst), dpp<kQuad1>(tr.h.prim));
+                    least(dpp<kQuad2>(__float_as_uint(tr.best)), dpp<kQuad2>(tr.h.inst), dpp<kQuad2>(tr.h.prim));
+                    if constexpr (W == 8)
+                        least(dpp<kHalfMirror>(__float_as_uint(tr.best)), dpp<kHalfMirror>(tr.h.inst),
+                              dpp<kHalfMirror>(tr.h.prim));
+                    tr.thi = tr.best - tr.t0;
+                    tr.thi = fmaf(fabsf(tr.thi), 2.4e-7f, tr.thi);
+                }
+            }
+            if (lane_in(m_leaf)) tr.cur = count > (uint32_t)W ? tr.cur - ((uint32_t)W << 28) + (uint32_t)W : RG_EMPTY;
+        }
+        __builtin_amdgcn_wave_barrier();  // the group's pushes come before its pops
+        uint64_t pop = ballot(tr.cur == RG_EMPTY) & has & ~stop;
+        const uint64_t end = ballot(tr.st.sp == 0) & pop;
+        pop &= ~end;
+        blas = (blas | m_inst) & ~hidden;
+        const uint64_t leave = ballot(tr.st.sp == tr.isp) & pop & blas;
+        if (lane_in(leave)) {
+            tr.world_frame();
+        }
+        blas &= ~leave;
+        if (lane_in(pop)) tr.cur = stk[--tr.st.sp];
+        uint64_t fin = end | stop;
+        // loop bound: see Tracer's callers
+        stalled = fin ? 0u : stalled + 1u;
+        if (stalled > kMaxSteps) fin = has;
+        has &= ~fin;
+        if (fin) {
+            if (lane_in(fin) && k == 0u) put(ray);
+        }
+    }
+}
+
 }  // namespace rgt
 
 // A top level as the kernels need it.
@@ -576,6 +774,7 @@ struct RgTraceArgs {
     uint32_t mask = RG_INST_MASK_ALL;  // visibility mask of every ray, unless ray_mask
     const uint8_t *ray_mask = nullptr;  // per ray (nullable)
     bool opt = false;              // masks / culling in effect (ray options or instance flags)
+    bool lanes = false;            // a lane per ray whatever the number of rays
     const RgTlasRef *jobs;
     const float *ray[8];           // ox oy oz dx dy dz tmin tmax
     int64_t n;                     // number of rays (upper bound if `count` is set)
