@@ -1565,8 +1565,9 @@ __global__ void k_ploc_relabel(int64_t n, int32_t *__restrict__ left, int32_t *_
 // Karras & Aila 2013 over the binary hierarchy.  A round visits every inner
 // node with at least three leaves below it after the nodes below it (a node
 // with two leaf children has one topology and is skipped): depths from the
-// root are taken when the round begins, deepest first, one launch per depth
-// and one wave per node; nodes of one depth have disjoint subtrees, and a
+// root are taken when the round begins, deepest first, one wave per node, a
+// launch per depth and one launch for the depths of at most kTreeletTop nodes
+// that end at the root; nodes of one depth have disjoint subtrees, and a
 // restructure never changes the set of leaves below its node, so the result
 // is that of any order that puts every node after those below it.
 // The treelet starts as the node's children; its inner leaf of largest
@@ -1580,46 +1581,59 @@ __global__ void k_ploc_relabel(int64_t n, int32_t *__restrict__ left, int32_t *_
 constexpr int kTreelet = 7;
 constexpr int kTreeletMaxRounds = 8;
 
-// The 127 non-empty subsets of 7 leaves ordered by size, then by value, and
-// where each size starts.  Subsets within the low m bits precede the others
-// of their size, so for a treelet of m leaves the subsets of size k are the
-// first C(m, k) entries of block k.
-struct TreeletSubsets {
-    uint8_t s[(1 << kTreelet) - 1];
-    uint8_t off[kTreelet + 2];
-    uint8_t binom[kTreelet + 1][kTreelet + 1];
+// One wave works on a treelet, in registers: lane k holds leaf k, lane L the
+// unions of the leaf subsets L and L | 64, and only the areas and costs that
+// the dynamic program reads across lanes are in LDS.  A launch of few nodes
+// lasts as long as one of them, and that is latency: nine dependent loads
+// (the node, its children, then one per growth step: the next leaf's box and
+// its children's indices together), the program's six levels, the rebuild.
+// The levels follow a schedule that is fixed for seven leaves (a smaller
+// treelet skips the larger levels and never reads the subsets with an absent
+// leaf): the subset and the splits of each lane are bytes of a table that is
+// read while the first loads are under way.  The rebuild walks the new
+// topology in scalar registers and then writes all its nodes at once.
+// A launch of one node: 21 us when one lane grew the treelet, the splits were
+// enumerated bit by bit and one lane rebuilt it; 7.5 us now, a third of it the
+// growth steps' loads.
+//
+// Splits of a subset S of k leaves: P (holding S's lowest leaf) and S \ P,
+// P = low | Q for the proper subsets Q of the rest in increasing order.  A
+// subset's 2^(k-1) - 1 splits are shared by kSplitLanes lanes, lane `part`
+// taking every kSplitLanes-th; where that leaves a lane without a split it
+// repeats its first, which changes nothing.
+constexpr int kSplitLanes[kTreelet + 1] = {0, 0, 0, 1, 1, 2, 8, 64};
+constexpr int kSplitIts[kTreelet + 1] = {0, 0, 0, 3, 7, 8, 4, 1};
+constexpr int kSplitByte[kTreelet + 1] = {0, 0, 0, 4, 7, 14, 22, 26};  // the lane's splits of a level
+struct TreeletSchedule {
+    uint8_t b[64][32];  // 0 .. 3: the lane's subset at sizes 3 .. 6 (0: none), then its splits by size
 };
 
 constexpr int popc_const(int v) { return v ? (v & 1) + popc_const(v >> 1) : 0; }
 
-constexpr TreeletSubsets make_treelet_subsets() {
-    TreeletSubsets t{};
-    int n = 0;
-    for (int k = 1; k <= kTreelet; ++k) {
-        t.off[k] = (uint8_t)n;
-        for (int S = 1; S < (1 << kTreelet); ++S)
-            if (popc_const(S) == k) t.s[n++] = (uint8_t)S;
-    }
-    t.off[kTreelet + 1] = (uint8_t)n;
-    for (int m = 0; m <= kTreelet; ++m)
-        for (int k = 0; k <= kTreelet; ++k) {
-            int c = 0;
-            for (int S = 0; S < (1 << m); ++S) c += popc_const(S) == k;
-            t.binom[m][k] = (uint8_t)c;
+constexpr TreeletSchedule make_treelet_schedule() {
+    TreeletSchedule t{};
+    for (int k = 3; k <= kTreelet; ++k) {
+        int lane = 0;
+        for (int S = 1; S < (1 << kTreelet); ++S) {
+            if (popc_const(S) != k) continue;
+            const int low = S & -S, rest = S ^ low, g = kSplitLanes[k], np = (1 << (k - 1)) - 1;
+            for (int part = 0; part < g; ++part, ++lane) {
+                if (k < kTreelet) t.b[lane][k - 3] = (uint8_t)S;
+                for (int i = 0; i < kSplitIts[k]; ++i) {
+                    int j = part + g * i;
+                    if (j >= np) j = part < np ? part : 0;
+                    int Q = 0, bit = 0;  // the bits of j on the set bits of rest, lowest first
+                    for (int q = 0; q < kTreelet; ++q)
+                        if ((rest >> q) & 1) Q |= ((j >> bit++) & 1) << q;
+                    t.b[lane][kSplitByte[k] + i] = (uint8_t)(low | Q);
+                }
+            }
         }
+    }
     return t;
 }
 
-__constant__ TreeletSubsets kSubsets = make_treelet_subsets();
-
-// The j-th subset of `mask` in increasing order: the bits of j placed on the
-// set bits of mask, lowest first.
-__device__ inline uint32_t deposit(uint32_t j, uint32_t mask) {
-    uint32_t r = 0u;
-    for (uint32_t b = mask; b; b &= b - 1u, j >>= 1)
-        if (j & 1u) r |= b & (0u - b);
-    return r;
-}
+__device__ const TreeletSchedule kSchedule = make_treelet_schedule();
 
 __device__ inline float area32(const float *lo, const float *hi) {
 #pragma clang fp contract(off)
@@ -1656,12 +1670,41 @@ __global__ void __launch_bounds__(kThreads) k_depths(int64_t m, const int32_t *_
     if (threadIdx.x == 0) atomicMax(hmax, bmax);
 }
 
+// Where each depth starts in the order, and the cursors cleared (one workgroup).
+__global__ void __launch_bounds__(kThreads) k_depth_starts(int64_t m, const uint32_t *__restrict__ hmax,
+                                                           const uint32_t *__restrict__ hcount,
+                                                           uint32_t *__restrict__ hstart,
+                                                           uint32_t *__restrict__ hcursor) {
+    __shared__ uint32_t sum[2][kThreads];
+    const int t = threadIdx.x;
+    const int64_t depths = (int64_t)*hmax + 1 < m ? (int64_t)*hmax + 1 : m;
+    uint32_t carry = 0u;
+    for (int64_t d0 = 0; d0 < depths; d0 += kThreads) {
+        const int64_t d = d0 + t;
+        const uint32_t c = d < depths ? hcount[d] : 0u;
+        int cur = 0;
+        sum[0][t] = c;
+        __syncthreads();
+        for (int k = 1; k < kThreads; k <<= 1) {
+            sum[cur ^ 1][t] = sum[cur][t] + (t >= k ? sum[cur][t - k] : 0u);
+            cur ^= 1;
+            __syncthreads();
+        }
+        if (d < depths) {
+            hstart[d] = carry + sum[cur][t] - c;
+            hcursor[d] = 0u;
+        }
+        carry += sum[cur][kThreads - 1];
+        __syncthreads();
+    }
+}
+
 // Inner nodes grouped by depth: order[hstart[d] ...] holds depth d (in no
 // particular order within a depth).  Positions are handed out per block and
 // depth, then per node within the block.
 __global__ void __launch_bounds__(kThreads) k_depth_scatter(int64_t m, const int32_t *__restrict__ depth,
                                                             const uint32_t *__restrict__ hstart, uint32_t *hcursor,
-                                                            int32_t dmax, int32_t *__restrict__ order) {
+                                                            int32_t *__restrict__ order) {
     __shared__ uint32_t bins[kDepthBins], base[kDepthBins];
     for (int k = threadIdx.x; k < kDepthBins; k += blockDim.x) bins[k] = 0u;
     __syncthreads();
@@ -1670,7 +1713,7 @@ __global__ void __launch_bounds__(kThreads) k_depth_scatter(int64_t m, const int
     uint32_t local = 0u;
     if (x < m) {
         d = depth[x];
-        if (d < 0 || d > dmax) d = -1;  // never once the host has checked the counts
+        if (d < 0 || d >= m) d = -1;  // never: a depth is below the inner node count
         else if (d < kDepthBins) local = atomicAdd(&bins[d], 1u);
     }
     __syncthreads();
@@ -1691,6 +1734,25 @@ __global__ void k_sizes_at(const int32_t *__restrict__ order, int64_t count, con
     const int32_t x = order[i];
     const int32_t a = left[x], b = right[x];
     size[x] = (a < 0 ? 1 : size[a]) + (b < 0 ? 1 : size[b]);
+}
+
+// The same for the depths `from` .. 0, of at most kSizesTop nodes each, in one
+// workgroup: a launch per depth otherwise, which lasts as long for a few nodes.
+constexpr int64_t kSizesTop = 4096;
+__global__ void __launch_bounds__(1024) k_sizes_top(const int32_t *__restrict__ order,
+                                                    const uint32_t *__restrict__ hstart,
+                                                    const uint32_t *__restrict__ hcount, int from,
+                                                    const int32_t *__restrict__ left,
+                                                    const int32_t *__restrict__ right, int32_t *size) {
+    for (int d = from; d >= 0; --d) {
+        const uint32_t at = hstart[d], n = hcount[d];
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const int32_t x = order[at + i];
+            const int32_t a = left[x], b = right[x];
+            size[x] = (a < 0 ? 1 : size[a]) + (b < 0 ? 1 : size[b]);
+        }
+        __syncthreads();
+    }
 }
 
 __global__ void k_leaf_boxes(const float *__restrict__ prim_box, const uint32_t *__restrict__ ids, int64_t n,
@@ -1799,166 +1861,242 @@ int64_t range_levels(int64_t nb) {
     return L;  // levels 0 .. L - 1: 2^(L-1) <= nb
 }
 
-__global__ void __launch_bounds__(64) k_treelet(const int32_t *__restrict__ order, int32_t *left, int32_t *right,
-                                                int32_t *parent_int, int32_t *parent_leaf, float *int_box,
-                                                const float *__restrict__ leaf_box) {
-    __shared__ float ulo[1 << kTreelet][3], uhi[1 << kTreelet][3];
-    __shared__ float area[1 << kTreelet], cost[1 << kTreelet];
-    __shared__ uint8_t split[1 << kTreelet];
-    __shared__ int32_t leaves[kTreelet], opened[kTreelet];
-    __shared__ float lbox[kTreelet][6], larea[kTreelet];
-    __shared__ int n_leaves, n_opened;
-    const int lane = threadIdx.x;
-    const int32_t node = order[blockIdx.x];
-    if (left[node] < 0 && right[node] < 0) return;  // two leaves: one topology, nothing to change
-    if (lane == 0) {
-        // Each treelet leaf's box and area are read once, when it joins, and
-        // kept in LDS: a growth step then waits on two loads (the opened
-        // node's children, then both their boxes) whatever the leaf count.
-        auto join = [&](int k0, int32_t c0, int k1, int32_t c1) {
-            const float *p0 = c0 < 0 ? leaf_box + 6 * (int64_t)(-c0 - 1) : int_box + 6 * (int64_t)c0;
-            const float *p1 = c1 < 0 ? leaf_box + 6 * (int64_t)(-c1 - 1) : int_box + 6 * (int64_t)c1;
-            float b0[6], b1[6];
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                b0[q] = p0[q];
-                b1[q] = p1[q];
-            }
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                lbox[k0][q] = b0[q];
-                lbox[k1][q] = b1[q];
-            }
-            leaves[k0] = c0;
-            leaves[k1] = c1;
-            larea[k0] = area32(b0, b0 + 3);
-            larea[k1] = area32(b1, b1 + 3);
-        };
-        int m = 2, r = 0;
-        join(0, left[node], 1, right[node]);
-        while (m < kTreelet) {
-            int bk = -1;
-            float ba = -INFINITY;
-            for (int k = 0; k < m; ++k) {
-                if (leaves[k] < 0) continue;   // a primitive cannot be opened
-                if (larea[k] > ba) {
-                    ba = larea[k];
-                    bk = k;
-                }
-            }
-            if (bk < 0) break;
-            const int32_t c = leaves[bk];
-            opened[r++] = c;
-            join(bk, left[c], m, right[c]);
-            ++m;
+struct TreeletShared {
+    float area[1 << kTreelet], cost[1 << kTreelet];
+    uint8_t split[1 << kTreelet];
+};
+
+// Orders one wave's LDS accesses across lanes (the LDS serves a wave's
+// accesses in order).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// lane data movement within 8 or 16 lanes (xor 1, xor 2, reversal of 8, of 16)
+template <int CTRL>
+__device__ inline int dpp(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+
+// The least (cost, split) over each group of G lanes.
+template <int G>
+__device__ inline void least_split(float &best, uint32_t &bp) {
+    auto take = [&](float v, uint32_t p) {
+        if (v < best || (v == best && p < bp)) {
+            best = v;
+            bp = p;
         }
-        for (int k = 1; k < r; ++k)  // ascending: the order the indices are handed out in
-            for (int q = k; q > 0 && opened[q - 1] > opened[q]; --q) {
-                const int32_t t = opened[q];
-                opened[q] = opened[q - 1];
-                opened[q - 1] = t;
-            }
-        n_leaves = m;
-        n_opened = r;
+    };
+    if (G >= 2) take(__int_as_float(dpp<0xB1>(__float_as_int(best))), (uint32_t)dpp<0xB1>((int)bp));
+    if (G >= 4) take(__int_as_float(dpp<0x4E>(__float_as_int(best))), (uint32_t)dpp<0x4E>((int)bp));
+    if (G >= 8) take(__int_as_float(dpp<0x141>(__float_as_int(best))), (uint32_t)dpp<0x141>((int)bp));
+    if (G >= 16) take(__int_as_float(dpp<0x140>(__float_as_int(best))), (uint32_t)dpp<0x140>((int)bp));
+    if (G >= 32) take(__shfl_xor(best, 16), (uint32_t)__shfl_xor((int)bp, 16));
+    if (G >= 64) take(__shfl_xor(best, 32), (uint32_t)__shfl_xor((int)bp, 32));
+}
+
+// The subsets of K leaves: their cheapest splits and costs.
+template <int K>
+__device__ __forceinline__ void treelet_level(TreeletShared &sh, const uint32_t (&w)[8], int lane) {
+#pragma clang fp contract(off)
+    auto byte = [&](int i) -> uint32_t { return (w[i >> 2] >> (8 * (i & 3))) & 0xFFu; };
+    const uint32_t S = K == kTreelet ? (1u << kTreelet) - 1u : byte(K - 3);
+    float best = INFINITY;
+    uint32_t bp = byte(kSplitByte[K]);
+    float v[kSplitIts[K]];
+#pragma unroll
+    for (int i = 0; i < kSplitIts[K]; ++i) {
+        const uint32_t P = byte(kSplitByte[K] + i);
+        v[i] = sh.cost[P] + sh.cost[S ^ P];
     }
-    __syncthreads();
-    const int m = n_leaves;
-    const uint32_t full = (1u << m) - 1u;
-    for (uint32_t S = (uint32_t)lane + 1u; S <= full; S += 64u) {
-        float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-        for (int k = 0; k < m; ++k) {
-            if (!((S >> k) & 1u)) continue;
-            const float *b = lbox[k];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                lo[q] = fminf(lo[q], b[q]);
-                hi[q] = fmaxf(hi[q], b[3 + q]);
-            }
+    for (int i = 0; i < kSplitIts[K]; ++i)
+        if (v[i] < best) {
+            best = v[i];
+            bp = byte(kSplitByte[K] + i);
         }
+    least_split<kSplitLanes[K]>(best, bp);
+    if (S != 0u && lane % kSplitLanes[K] == 0) {
+        sh.cost[S] = sh.area[S] + best;
+        sh.split[S] = (uint8_t)bp;
+    }
+    wave_sync();
+}
+
+// The treelet of one node, by one wave.  No loads or stores of the hierarchy
+// but of the node and the nodes below it, and of parents' links to the node's
+// descendants.
+__device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *left, int32_t *right, int32_t *parent_int,
+                                    int32_t *parent_leaf, float *int_box, const float *__restrict__ leaf_box,
+                                    TreeletShared &sh, int lane) {
+    const int32_t node = __builtin_amdgcn_readfirstlane(*order_at);
+    uint32_t w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = reinterpret_cast<const uint32_t *>(kSchedule.b[lane])[q];
+    const int32_t c0 = __builtin_amdgcn_readfirstlane(left[node]), c1 = __builtin_amdgcn_readfirstlane(right[node]);
+    if (c0 < 0 && c1 < 0) return;  // two leaves: one topology, nothing to change
+    // this lane's treelet leaf, its children and box, and its area's bits if
+    // it can be opened (areas are not negative; -1: it cannot)
+    int32_t c = lane == 0 ? c0 : c1, cl = 0, cr = 0, key = -1, op = 0x7FFFFFFF;
+    float b[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    auto join = [&]() {
+        const float *p = c < 0 ? leaf_box + 6 * (int64_t)(-c - 1) : int_box + 6 * (int64_t)c;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) b[q] = p[q];
+        key = -1;
+        if (c >= 0) {
+            cl = left[c];
+            cr = right[c];
+            const float a = area32(b, b + 3);
+            if (a >= 0.0f) key = __float_as_int(a);
+        }
+    };
+    if (lane < 2) join();
+    int m = 2;
+    while (m < kTreelet) {
+        int t = key;  // lanes m .. 7 hold -1
+        t = max(t, dpp<0xB1>(t));
+        t = max(t, dpp<0x4E>(t));
+        t = max(t, dpp<0x141>(t));
+        const int32_t top = __builtin_amdgcn_readfirstlane(t);
+        if (top < 0) break;  // only primitives
+        const int bk = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(key == top)) - 1;
+        const int32_t o = __builtin_amdgcn_readlane(c, bk), ol = __builtin_amdgcn_readlane(cl, bk),
+                      orr = __builtin_amdgcn_readlane(cr, bk);
+        if (lane == m - 2) op = o;
+        if (lane == bk) c = ol;
+        if (lane == m) c = orr;
+        if (lane == bk || lane == m) join();
+        ++m;
+    }
+    const uint32_t full = (1u << m) - 1u;
+    // the opened nodes in ascending order: lane q's is the q-th it hands out
+    int32_t sorted = 0;
+    {
+        int r = 0;
+#pragma unroll
+        for (int q = 0; q < kTreelet - 2; ++q) r += __builtin_amdgcn_readlane(op, q) < op ? 1 : 0;
+#pragma unroll
+        for (int q = 0; q < kTreelet - 2; ++q) {
+            const int32_t v = __builtin_amdgcn_readlane(op, q);
+            const int rq = __builtin_amdgcn_readlane(r, q);
+            if (q < m - 2 && lane == rq) sorted = v;
+        }
+    }
+    // unions of the subsets `lane` (leaves 0 .. 5) and `lane` | 64
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, lo6[3], hi6[3];
+#pragma unroll
+    for (int k = 0; k < kTreelet; ++k) {
+        const bool in = (lane >> k) & 1;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            ulo[S][q] = lo[q];
-            uhi[S][q] = hi[q];
-        }
-        area[S] = area32(lo, hi);
-        cost[S] = 0.0f;
-        split[S] = 0;
-    }
-    __syncthreads();
-    // Subsets of one size at a time.  A subset S splits into P (holding its
-    // lowest leaf) and S \ P; P = low | Q for the proper subsets Q of the rest,
-    // Q the j-th in increasing order.  The first cheapest split in that order
-    // is kept.  The subsets of a size share the wave: g lanes per subset,
-    // each taking every g-th j, then the least (cost, j) over the group.
-    for (int k = 2; k <= m; ++k) {
-        const int nk = kSubsets.binom[m][k];
-        const uint32_t np = (1u << (k - 1)) - 1u;   // splits of a k-subset
-        int g = 1;
-        while (2 * g * nk <= 64 && (uint32_t)g < np) g *= 2;
-        const int si = lane / g, part = lane % g;
-        uint32_t S = 0u, low = 0u, rest = 0u, bj = 0xFFFFFFFFu;
-        float best = INFINITY;
-        if (si < nk) {
-            S = kSubsets.s[kSubsets.off[k] + si];
-            low = S & (0u - S);
-            rest = S ^ low;
-            for (uint32_t j = (uint32_t)part; j < np; j += (uint32_t)g) {
-                const uint32_t P = low | deposit(j, rest);
-                const float v = cost[P] + cost[S ^ P];
-                if (v < best) {
-                    best = v;
-                    bj = j;
-                }
+            const float bl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b[q]), k));
+            const float bh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b[3 + q]), k));
+            if (k < kTreelet - 1) {
+                lo[q] = in ? fminf(lo[q], bl) : lo[q];
+                hi[q] = in ? fmaxf(hi[q], bh) : hi[q];
+            } else {
+                lo6[q] = fminf(lo[q], bl);
+                hi6[q] = fmaxf(hi[q], bh);
             }
         }
-        for (int d = 1; d < g; d <<= 1) {
-            const float ov = __shfl_xor(best, d);
-            const uint32_t oj = __shfl_xor(bj, d);
-            if (ov < best || (ov == best && oj < bj)) {
-                best = ov;
-                bj = oj;
-            }
-        }
-        if (si < nk && part == 0) {
-            cost[S] = area[S] + best;
-            split[S] = (uint8_t)(bj == 0xFFFFFFFFu ? 0u : (low | deposit(bj, rest)));
-        }
-        __syncthreads();
     }
-    if (lane != 0) return;
-    // rebuild: entries (subset, parent, side) popped in pre-order; the stack
-    // lives in LDS, which keeps the kernel's registers low enough for more
-    // waves per SIMD (the walk is one lane's)
-    __shared__ uint32_t st_set[2 * kTreelet];
-    __shared__ int32_t st_parent[2 * kTreelet];
-    __shared__ int32_t st_side[2 * kTreelet];
-    int sp = 0, next = 0;
-    st_set[sp] = full ^ split[full]; st_parent[sp] = node; st_side[sp] = 1; ++sp;
-    st_set[sp] = split[full]; st_parent[sp] = node; st_side[sp] = 0; ++sp;
-    while (sp > 0) {
-        --sp;
-        const uint32_t T = st_set[sp];
-        const int32_t parent = st_parent[sp];
-        const int side = st_side[sp];
-        int32_t child;
-        if ((T & (T - 1u)) == 0u) {
-            child = leaves[__ffs((int)T) - 1];
-        } else {
-            if (next >= n_opened || sp + 2 > 2 * kTreelet) return;  // never: m - 2 opened nodes, depth < m
-            child = opened[next++];
-            float *b = int_box + 6 * (int64_t)child;
+    // a subset of two leaves has one split, one leaf none
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                b[q] = ulo[T][q];
-                b[3 + q] = uhi[T][q];
-            }
-            st_set[sp] = T ^ split[T]; st_parent[sp] = child; st_side[sp] = 1; ++sp;
-            st_set[sp] = split[T]; st_parent[sp] = child; st_side[sp] = 0; ++sp;
+    for (int h = 0; h < 2; ++h) {
+        const int S = lane | (h << 6);
+        const float a = h ? area32(lo6, hi6) : area32(lo, hi);
+        sh.area[S] = a;
+        sh.cost[S] = __popc(S) == 2 ? a : 0.0f;
+        sh.split[S] = (uint8_t)(S & -S);
+    }
+    wave_sync();
+    if (m >= 3) treelet_level<3>(sh, w, lane);
+    if (m >= 4) treelet_level<4>(sh, w, lane);
+    if (m >= 5) treelet_level<5>(sh, w, lane);
+    if (m >= 6) treelet_level<6>(sh, w, lane);
+    if (m >= 7) treelet_level<7>(sh, w, lane);
+    // Rebuild.  The new inner nodes in pre-order: lane q takes the q-th, its
+    // subset T and the part P of it that goes left.  An inner right child
+    // comes after the popc(P) - 1 inner nodes on the left.
+    const int32_t splits = sh.split[lane] | (sh.split[lane | 64] << 8);
+    uint32_t T = full, myT = 0u, myP = 0u;
+    uint64_t stack = 0ull;  // inner right subsets still to visit, a byte each
+    for (int q = 0; q < m - 1; ++q) {
+        const uint32_t P = ((uint32_t)__builtin_amdgcn_readlane(splits, (int)(T & 63u)) >> ((T >> 6) * 8)) & 0xFFu;
+        const uint32_t R = T ^ P;
+        if (lane == q) {
+            myT = T;
+            myP = P;
         }
-        if (side == 0) left[parent] = child;
-        else right[parent] = child;
-        if (child < 0) parent_leaf[-child - 1] = parent;
-        else parent_int[child] = parent;
+        const bool li = (P & (P - 1u)) != 0u, ri = (R & (R - 1u)) != 0u;
+        if (li) {
+            if (ri) stack = (stack << 8) | R;
+            T = P;
+        } else if (ri) {
+            T = R;
+        } else {
+            T = (uint32_t)stack & 0xFFu;
+            stack >>= 8;
+        }
+    }
+    const uint32_t R = myT ^ myP;
+    const int np = __popc(myP);
+    const int32_t leaf_l = __shfl(c, __ffs((int)myP) - 1), leaf_r = __shfl(c, __ffs((int)R) - 1);
+    const int32_t in_l = __shfl(sorted, lane), in_r = __shfl(sorted, lane + np - 1), in_me = __shfl(sorted, lane - 1);
+    float nb[6];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float a = __shfl(lo[q], (int)(myT & 63u)), a6 = __shfl(lo6[q], (int)(myT & 63u));
+        const float z = __shfl(hi[q], (int)(myT & 63u)), z6 = __shfl(hi6[q], (int)(myT & 63u));
+        nb[q] = myT & 64u ? a6 : a;
+        nb[3 + q] = myT & 64u ? z6 : z;
+    }
+    if (lane < m - 1) {
+        const int32_t me = lane == 0 ? node : in_me;
+        const int32_t l = np == 1 ? leaf_l : in_l, r = (R & (R - 1u)) == 0u ? leaf_r : in_r;
+        left[me] = l;
+        right[me] = r;
+        if (l < 0) parent_leaf[-l - 1] = me;
+        else parent_int[l] = me;
+        if (r < 0) parent_leaf[-r - 1] = me;
+        else parent_int[r] = me;
+        if (lane > 0) {
+            float *p = int_box + 6 * (int64_t)me;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) p[q] = nb[q];
+        }
+    }
+}
+
+// The nodes of one depth, a wave each.
+__global__ void __launch_bounds__(64)
+k_treelet(const int32_t *__restrict__ order, int32_t *left, int32_t *right, int32_t *parent_int, int32_t *parent_leaf,
+          float *int_box, const float *__restrict__ leaf_box) {
+    __shared__ TreeletShared sh;
+    treelet_node(order + blockIdx.x, left, right, parent_int, parent_leaf, int_box, leaf_box, sh, threadIdx.x);
+}
+
+// The nodes of the depths `from` .. 0 in one workgroup, for depths of at most
+// as many nodes as it has waves: 7 us a depth, where a launch takes as long
+// and the next waits two more for it; at 32 nodes a wave has two, which takes
+// as long as two launches.
+constexpr int kTopWaves = 16;
+constexpr uint32_t kTreeletTop = kTopWaves;
+__global__ void __launch_bounds__(64 * kTopWaves) k_treelet_top(const int32_t *__restrict__ order,
+                                                                const uint32_t *__restrict__ hstart,
+                                                                const uint32_t *__restrict__ hcount, int from,
+                                                                int32_t *left, int32_t *right, int32_t *parent_int,
+                                                                int32_t *parent_leaf, float *int_box,
+                                                                const float *__restrict__ leaf_box) {
+    __shared__ TreeletShared sh[kTopWaves];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int d = from; d >= 0; --d) {
+        const uint32_t at = hstart[d], n = hcount[d];
+        for (uint32_t i = (uint32_t)wave; i < n; i += kTopWaves)
+            treelet_node(order + at + i, left, right, parent_int, parent_leaf, int_box, leaf_box, sh[wave], lane);
+        __syncthreads();
     }
 }
 
@@ -2398,10 +2536,10 @@ bool carve(RgArena &a, int64_t n, int32_t builder, LbvhScratch &s) {
     }
     s.height = a.take<int32_t>(ni);
     s.order = a.take<int32_t>(ni);
-    s.hcount = a.take<uint32_t>(n + 1);
+    s.hmax = a.take<uint32_t>(n + 2);  // the deepest depth, then the counts
+    s.hcount = s.hmax + 1;
     s.hcursor = a.take<uint32_t>(n + 1);
     s.hstart = a.take<uint32_t>(n + 1);
-    s.hmax = a.take<uint32_t>(8);
     if (builder != RG_BUILDER_PLOC) {
         const int64_t nbr = (n + kRangeLeaves - 1) / kRangeLeaves;
         s.pre = a.take<float>(6 * n);
@@ -2420,29 +2558,41 @@ struct DepthOrder {
 };
 
 rg_status depth_order(LbvhScratch &s, int64_t m, hipStream_t st, DepthOrder &o) {
-    k_fill_u32<<<rg_blocks(m + 2, kThreads), kThreads, 0, st>>>(s.hcount, 0u, m + 2);
-    k_fill_u32<<<1, 64, 0, st>>>(s.hmax, 0u, 1);
+    k_fill_u32<<<rg_blocks(m + 3, kThreads), kThreads, 0, st>>>(s.hmax, 0u, m + 3);  // and hcount
     k_depths<<<rg_blocks(m, kThreads), kThreads, 0, st>>>(m, s.pint, s.height, s.hcount, s.hmax);
+    k_depth_starts<<<1, kThreads, 0, st>>>(m, s.hmax, s.hcount, s.hstart, s.hcursor);
+    k_depth_scatter<<<rg_blocks(m, kThreads), kThreads, 0, st>>>(m, s.height, s.hstart, s.hcursor, s.order);
     RG_LAUNCH_CHECK();
-    RG_HIP(hipMemcpyAsync(&o.dmax, s.hmax, 4, hipMemcpyDeviceToHost, st));
+    // one wait: the deepest depth and the counts that most hierarchies have
+    uint32_t head[1 + kDepthBins];
+    const int64_t words = m < kDepthBins ? 1 + m : 1 + kDepthBins;
+    RG_HIP(hipMemcpyAsync(head, s.hmax, 4 * words, hipMemcpyDeviceToHost, st));
     RG_HIP(hipStreamSynchronize(st));
+    o.dmax = head[0];
     if ((int64_t)o.dmax >= m) return RG_ERR_HIP;  // never: a depth is below the inner node count
-    o.cnt.assign(o.dmax + 1, 0u);
+    o.cnt.assign(head + 1, head + words);
+    o.cnt.resize(o.dmax + 1);
+    if (o.dmax >= (uint32_t)kDepthBins) {
+        RG_HIP(hipMemcpyAsync(o.cnt.data() + kDepthBins, s.hcount + kDepthBins, 4 * (o.dmax + 1 - kDepthBins),
+                              hipMemcpyDeviceToHost, st));
+        RG_HIP(hipStreamSynchronize(st));
+    }
     o.start.assign(o.dmax + 1, 0u);
-    RG_HIP(hipMemcpyAsync(o.cnt.data(), s.hcount, 4 * (o.dmax + 1), hipMemcpyDeviceToHost, st));
-    RG_HIP(hipStreamSynchronize(st));
     uint64_t total = 0;
     for (uint32_t d = 0; d <= o.dmax; ++d) {
         o.start[d] = (uint32_t)total;
         total += o.cnt[d];
     }
     if ((int64_t)total != m) return RG_ERR_HIP;  // never: every inner node has one depth
-    RG_HIP(hipMemcpyAsync(s.hstart, o.start.data(), 4 * (o.dmax + 1), hipMemcpyHostToDevice, st));
-    k_fill_u32<<<rg_blocks(o.dmax + 1, kThreads), kThreads, 0, st>>>(s.hcursor, 0u, o.dmax + 1);
-    k_depth_scatter<<<rg_blocks(m, kThreads), kThreads, 0, st>>>(m, s.height, s.hstart, s.hcursor, (int32_t)o.dmax,
-                                                                  s.order);
-    RG_LAUNCH_CHECK();
     return RG_OK;
+}
+
+// The deepest depth from which on up to the root no depth has more than
+// `most` nodes (the root's has one).
+int64_t top_depths(const DepthOrder &o, uint32_t most) {
+    int64_t d = 0;
+    while (d < (int64_t)o.dmax && o.cnt[d + 1] <= most) ++d;
+    return d;
 }
 
 // Renumbers the leaves of the binary hierarchy in s (n >= 2) in the tree's
@@ -2453,11 +2603,12 @@ rg_status relabel_leaves(LbvhScratch &s, int64_t n, const uint32_t *ids, uint32_
     DepthOrder o;
     rg_status r = depth_order(s, n - 1, st, o);
     if (r != RG_OK) return r;
-    for (int64_t d = o.dmax; d >= 0; --d)
+    const int64_t top = top_depths(o, kSizesTop);
+    for (int64_t d = o.dmax; d > top; --d)
         k_sizes_at<<<rg_blocks(o.cnt[d], kThreads), kThreads, 0, st>>>(s.order + o.start[d], o.cnt[d], s.left,
                                                                         s.right, s.size);
+    k_sizes_top<<<1, 1024, 0, st>>>(s.order, s.hstart, s.hcount, (int)top, s.left, s.right, s.size);
     RG_LAUNCH_CHECK();
-    RG_HIP(hipStreamSynchronize(st));  // the host vectors of `o` go away on return
     k_ploc_ranks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(n, s.left, s.pint, s.pleaf, s.size, ids,
                                                                s.leaf_box, s.rank, s.first, s.last, ids_out,
                                                                box_out);
@@ -2513,17 +2664,15 @@ rg_status treelet_build(int64_t n, int rounds, const uint32_t *ids, uint32_t *id
         rg_status r = depth_order(s, m, st, o);
         if (r != RG_OK) return r;
         if (o.dmax < 1u) break;  // only the root: no inner node has three leaves below it
-        const std::vector<uint32_t> &cnt = o.cnt, &start = o.start;
-        const uint32_t dmax = o.dmax;
         // deepest first: a node's descendants are deeper, nodes of one depth
         // have disjoint subtrees
-        for (int64_t d = dmax; d >= 0; --d) {
-            if (cnt[d] == 0u) continue;
-            k_treelet<<<cnt[d], 64, 0, st>>>(s.order + start[d], s.left, s.right, s.pint, s.pleaf, s.int_box,
-                                             s.leaf_box);
-        }
+        const int64_t top = top_depths(o, kTreeletTop);
+        for (int64_t d = o.dmax; d > top; --d)
+            k_treelet<<<o.cnt[d], 64, 0, st>>>(s.order + o.start[d], s.left, s.right, s.pint, s.pleaf, s.int_box,
+                                               s.leaf_box);
+        k_treelet_top<<<1, 64 * kTopWaves, 0, st>>>(s.order, s.hstart, s.hcount, (int)top, s.left, s.right, s.pint,
+                                                    s.pleaf, s.int_box, s.leaf_box);
         RG_LAUNCH_CHECK();
-        RG_HIP(hipStreamSynchronize(st));  // the host vectors above are reused next round
     }
     return relabel_leaves(s, n, ids, ids_out, s.cbox[0], st);
 }
