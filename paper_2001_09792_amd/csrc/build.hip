@@ -669,30 +669,45 @@ __device__ inline uint32_t collapse_links(const int32_t C[W], int m, const int32
     return inner;
 }
 
-// Writes a wide node: the children's boxes (empty slots inverted) and links,
-// assembled in registers and stored 16 bytes at a time (a node is 64-byte
-// aligned): 2W stores per node instead of 8W.
+// A wide node in registers: the children's boxes (empty slots inverted),
+// then their links, stored 16 bytes at a time (a node is 64-byte aligned): 2W
+// stores per node instead of 8W.  A slot past the m >= 1 children reads the
+// first child's box and drops it: no branch between the loads, which a wave
+// would wait at.
 template <int W>
-__device__ inline void write_wide_node(RgNode<W> *nd, const int32_t C[W], int m, const uint32_t link[W],
-                                       const float *__restrict__ int_box, const float *__restrict__ leaf_box) {
+__device__ inline void gather_boxes(float b[W][6], const int32_t C[W], int m, const float *int_box,
+                                    const float *leaf_box) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const int32_t c = k < m ? C[k] : C[0];
+        const float *src = (c < 0 ? leaf_box : int_box) + 6 * (int64_t)(c < 0 ? -c - 1 : c);
+#pragma unroll
+        for (int z = 0; z < 6; ++z) b[k][z] = src[z];
+    }
+}
+
+template <int W>
+__device__ inline void store_wide_node(RgNode<W> *nd, const float b[W][6], int m, const uint32_t link[W]) {
     uint32_t w[8 * W];
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        if (k < m) {
-            const int32_t c = C[k];
-            const float *src = c < 0 ? leaf_box + 6 * (int64_t)(-c - 1) : int_box + 6 * (int64_t)c;
 #pragma unroll
-            for (int z = 0; z < 6; ++z) b[z] = src[z];
-        }
-#pragma unroll
-        for (int z = 0; z < 6; ++z) w[z * W + k] = __float_as_uint(b[z]);
+        for (int z = 0; z < 6; ++z)
+            w[z * W + k] = __float_as_uint(k < m ? b[k][z] : (z < 3 ? INFINITY : -INFINITY));
         w[6 * W + k] = link[k];
         w[7 * W + k] = 0u;
     }
     uint4 *dst = reinterpret_cast<uint4 *>(nd);
 #pragma unroll
     for (int q = 0; q < 2 * W; ++q) dst[q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+}
+
+template <int W>
+__device__ inline void write_wide_node(RgNode<W> *nd, const int32_t C[W], int m, const uint32_t link[W],
+                                       const float *int_box, const float *leaf_box) {
+    float b[W][6];
+    gather_boxes<W>(b, C, m, int_box, leaf_box);
+    store_wide_node<W>(nd, b, m, link);
 }
 
 // The children every inner node of the binary hierarchy would get as the
@@ -719,84 +734,188 @@ __global__ void k_wide_plan(const int32_t *__restrict__ left, const int32_t *__r
     }
 }
 
-// One thread per node of the level (queue items: node index, binary node it
-// stands for).  Children that stay inner nodes join the next level's queue:
-// one counter add per wave, and a child's node index is the next level's
-// first index plus its queue slot.
+// The bookkeeping of a level-by-level collapse (ring): [0, R) node count of
+// level l at l % R, [R, 2R) first node index of level l at R + l % R, [2R]
+// error flags.
+struct CollapseArgs {
+    const int32_t *wch;
+    const uint32_t *wlink;
+    const uint8_t *winner;
+    const float *int_box, *leaf_box;
+    uint2 *q[2];          // queue of level l at l & 1
+    uint32_t *ring;
+    void *nodes;
+    uint32_t *parents, *levels;
+    uint32_t cap;
+};
+
+// A barrier that orders the block's LDS accesses only.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Exclusive sums of `nc` over a block of T threads, and the block's total.
+// Every thread of the block must call it.
+template <int T>
+__device__ inline uint32_t block_excl(uint32_t nc, uint32_t *wave_sum /* LDS, T / 64 */, uint32_t &total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t incl = nc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) wave_sum[w] = incl;
+    lds_barrier();
+    uint32_t before = 0u;
+    total = 0u;
+#pragma unroll
+    for (int v = 0; v < T / 64; ++v) {
+        const uint32_t x = wave_sum[v];
+        if (v < w) before += x;
+        total += x;
+    }
+    return before + incl - nc;
+}
+
+// A queue item of a level: the wide node's children, and how many of them
+// join the next level's queue.
 template <int W>
-__global__ void k_collapse(const int32_t *__restrict__ wch, const uint32_t *__restrict__ wlink,
-                           const uint8_t *__restrict__ winner, const float *__restrict__ int_box,
-                           const float *__restrict__ leaf_box, const uint2 *__restrict__ q_in,
-                           uint2 *__restrict__ q_out, uint32_t *ring, int level, RgNode<W> *__restrict__ nodes,
-                           uint32_t *__restrict__ parents, uint32_t *__restrict__ levels, uint32_t cap) {
-    // ring: [0, R) node count of level l at l % R, [R, 2R) first node index of
-    // level l at R + l % R, [2R] error flags.  A level's kernel sets up the
-    // next level's first index and clears the count two levels ahead, so
-    // levels can be launched back to back with no host step between them.
-    uint32_t *count_in = ring + level % kCollapseRing, *q_out_count = ring + (level + 1) % kCollapseRing;
-    uint32_t cnt = *count_in;
-    if (cnt > cap) cnt = cap;
-    const uint32_t next_base = ring[kCollapseRing + level % kCollapseRing] + cnt;
+struct CollapseItem {
+    uint2 item;           // node index, binary node it stands for
+    int32_t C[W];
+    uint32_t link[W], inner;
+    float b[W][6];
+    int m;
+};
+
+// The children's boxes are asked for here, so that they arrive while the
+// queue slots are worked out.
+template <int W>
+__device__ inline void collapse_load(const CollapseArgs &a, uint2 item, bool active, CollapseItem<W> &x) {
+    x.item = item;
+    x.inner = 0u;
+    x.m = 0;
+    if (!active) return;
+    const int64_t b = item.y;
+    x.inner = a.winner[b];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        x.C[k] = a.wch[W * b + k];
+        x.link[k] = a.wlink[W * b + k];
+        if (((x.inner >> k) & 1u) || x.link[k] != RG_EMPTY) x.m = k + 1;
+    }
+    gather_boxes<W>(x.b, x.C, x.m, a.int_box, a.leaf_box);
+}
+
+// A child that stays an inner node takes the next slot of the next level's
+// queue; its node index is that level's first index plus the slot.
+template <int W>
+__device__ inline void collapse_store(const CollapseArgs &a, uint2 *q_out, uint32_t slot, uint32_t next_base,
+                                      bool active, CollapseItem<W> &x) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        if (!((x.inner >> k) & 1u)) continue;
+        const uint32_t nn = next_base + slot;
+        if (nn < a.cap && slot < a.cap) {  // a BVH2 has n-1 inner nodes: never exceeded
+            q_out[slot] = make_uint2(nn, (uint32_t)x.C[k]);
+            if (a.parents) a.parents[nn] = (x.item.x << 3) | (uint32_t)k;
+            x.link[k] = nn;
+        } else {
+            atomicOr(a.ring + 2 * kCollapseRing, 4u);
+        }
+        ++slot;
+    }
+    if (active) store_wide_node<W>(reinterpret_cast<RgNode<W> *>(a.nodes) + x.item.x, x.b, x.m, x.link);
+}
+
+// One thread per node of the level.  The next level's queue is one counter
+// for the whole device, and its adds are served one after the other at some
+// 15 ns each: a block adds once for its kCollapseT nodes (a wave's adds made
+// the largest level of 627,200 triangles, width 4, take 28 us; 13 us now).
+constexpr int kCollapseT = 512;
+template <int W>
+__global__ void __launch_bounds__(kCollapseT) k_collapse(CollapseArgs a, int level) {
+    __shared__ uint32_t wave_sum[kCollapseT / 64], first_slot;
+    // A level's kernel sets up the next level's first index and clears the
+    // count two levels ahead, so levels can be launched back to back with no
+    // host step between them.
+    uint32_t *q_out_count = a.ring + (level + 1) % kCollapseRing;
+    uint32_t cnt = a.ring[level % kCollapseRing];
+    if (cnt > a.cap) cnt = a.cap;
+    const uint32_t next_base = a.ring[kCollapseRing + level % kCollapseRing] + cnt;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ring[kCollapseRing + (level + 1) % kCollapseRing] = next_base;
-        ring[(level + 2) % kCollapseRing] = 0u;
+        a.ring[kCollapseRing + (level + 1) % kCollapseRing] = next_base;
+        a.ring[(level + 2) % kCollapseRing] = 0u;
         // the level table (first node of each level, then the node count):
         // launches past the last level write the node count again
-        if (levels && level + 1 <= RG_LEVELS_CAP) levels[level + 1] = next_base;
+        if (a.levels && level + 1 <= RG_LEVELS_CAP) a.levels[level + 1] = next_base;
     }
-    uint32_t *err = ring + 2 * kCollapseRing;
-    const int lane = threadIdx.x & 63;
-    // the loop bound is the same for every lane of a block, so whole waves
-    // take part in the scan below
-    for (uint32_t base = blockIdx.x * blockDim.x; base < cnt; base += gridDim.x * blockDim.x) {
+    // the loop bound is the same for every lane of a block, so whole blocks
+    // take part in the sums below
+    for (uint32_t base = blockIdx.x * kCollapseT; base < cnt; base += gridDim.x * kCollapseT) {
         const uint32_t qi = base + threadIdx.x;
         const bool active = qi < cnt;
-        int32_t C[W];
-        uint32_t link[W];
-        uint2 item = make_uint2(0u, 0u);
-        int m = 0;
-        uint32_t inner = 0u;
-        if (active) {
-            item = q_in[qi];
-            const int64_t b = item.y;
-            inner = winner[b];
-#pragma unroll
-            for (int k = 0; k < W; ++k) {
-                C[k] = wch[W * b + k];
-                link[k] = wlink[W * b + k];
-                if (((inner >> k) & 1u) || link[k] != RG_EMPTY) m = k + 1;
-            }
-        }
-        // queue slots: an exclusive scan of the inner-child counts over the wave
-        const uint32_t nc = __popc(inner);
-        uint32_t incl = nc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
-        const uint32_t total = __shfl(incl, 63, 64);
-        uint32_t wbase = 0u;
-        if (lane == 63 && total) wbase = atomicAdd(q_out_count, total);
-        wbase = __shfl(wbase, 63, 64);
-        uint32_t slot = wbase + incl - nc;
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            if (!((inner >> k) & 1u)) continue;
-            const uint32_t nn = next_base + slot;
-            if (nn < cap && slot < cap) {  // a BVH2 has n-1 inner nodes: never exceeded
-                q_out[slot] = make_uint2(nn, (uint32_t)C[k]);
-                if (parents) parents[nn] = (item.x << 3) | (uint32_t)k;
-                link[k] = nn;
-            } else {
-                atomicOr(err, 4u);
-            }
-            ++slot;
-        }
-        if (!active) continue;
-        write_wide_node<W>(nodes + item.x, C, m, link, int_box, leaf_box);
+        CollapseItem<W> x;
+        collapse_load<W>(a, active ? a.q[level & 1][qi] : make_uint2(0u, 0u), active, x);
+        uint32_t total;
+        const uint32_t at = block_excl<kCollapseT>((uint32_t)__popc(x.inner), wave_sum, total);
+        if (threadIdx.x == 0) first_slot = total ? atomicAdd(q_out_count, total) : 0u;
+        lds_barrier();
+        collapse_store<W>(a, a.q[(level + 1) & 1], first_slot + at, next_base, active, x);
     }
 }
+
+// The levels that have at most kCollapseTop nodes whatever the hierarchy
+// (W^l of them), 0 .. collapse_top(W) - 1, in one workgroup, which starts the
+// bookkeeping: a level takes its two dependent loads and no launch.  The
+// queues between them are in LDS and the barriers order LDS alone, so no
+// level waits for the stores of the one before.
+constexpr int kCollapseTop = 512;
+constexpr int collapse_top(int W) {
+    int l = 1;
+    for (int64_t c = W; c <= kCollapseTop; c *= W) ++l;
+    return l;
+}
+
+template <int W>
+__global__ void __launch_bounds__(kCollapseTop) k_collapse_top(CollapseArgs a) {
+    __shared__ uint32_t wave_sum[2][kCollapseTop / 64];
+    __shared__ uint2 queue[2][kCollapseTop];
+    const int t = threadIdx.x;
+    if (t == 0) {
+        queue[0][0] = make_uint2(0u, 0u);
+        if (a.parents) a.parents[0] = RG_MISS;  // the root
+        if (a.levels) a.levels[0] = 0u;
+    }
+    lds_barrier();
+    uint32_t cnt = 1u, next_base = 1u;
+    for (int level = 0; level < collapse_top(W); ++level) {
+        const bool active = (uint32_t)t < cnt;
+        CollapseItem<W> x;
+        collapse_load<W>(a, active ? queue[level & 1][t] : make_uint2(0u, 0u), active, x);
+        uint32_t total;
+        const uint32_t at = block_excl<kCollapseTop>((uint32_t)__popc(x.inner), wave_sum[level & 1], total);
+        if (level + 1 < collapse_top(W)) collapse_store<W>(a, queue[(level + 1) & 1], at, next_base, active, x);
+        else collapse_store<W>(a, a.q[(level + 1) & 1], at, next_base, active, x);
+        // the bookkeeping as a launch per level leaves it: this level's count
+        // stays, the next level's first index and count, a cleared count after
+        if (t == 0) {
+            a.ring[level % kCollapseRing] = cnt;
+            a.ring[(level + 1) % kCollapseRing] = total;
+            a.ring[(level + 2) % kCollapseRing] = 0u;
+            a.ring[kCollapseRing + (level + 1) % kCollapseRing] = next_base;
+            if (level == 0) a.ring[2 * kCollapseRing] = 0u;
+            if (a.levels && level + 1 <= RG_LEVELS_CAP) a.levels[level + 1] = next_base;
+        }
+        cnt = total < a.cap ? total : a.cap;
+        next_base += cnt;
+        lds_barrier();  // the queue of the next level
+    }
+}
+static_assert(collapse_top(2) <= kCollapseRing - 3, "the ring holds the levels of the first launch");
 
 // Single-primitive structure: one root node with one leaf child.
 template <int W>
@@ -814,14 +933,6 @@ __global__ void k_single_root(const float *__restrict__ leaf_box, RgNode<W> *nod
         nd->child[k] = RG_EMPTY;
     }
     nd->pad[k] = 0u;
-}
-
-__global__ void k_collapse_init(uint2 *q, uint32_t *ring, uint32_t *parents, uint32_t *levels) {
-    q[0] = make_uint2(0u, 0u);
-    for (int k = 0; k <= 2 * kCollapseRing; ++k) ring[k] = 0u;
-    ring[0] = 1u;  // level 0: the root, node 0
-    if (parents) parents[0] = RG_MISS;  // the root
-    if (levels) levels[0] = 0u;
 }
 
 // ------------------------------------------------ top-level instances
@@ -2688,16 +2799,8 @@ struct CollapseState {
     int32_t batch = 0;     // levels in the batch last launched
     int32_t depth = 0;     // the number of levels, once known
     uint32_t known = 1;    // size of level d
-    uint32_t cap = 0;
     uint64_t n_nodes = 1;  // nodes of the levels known so far
-    const int32_t *wch;
-    const uint32_t *wlink;
-    const uint8_t *winner;
-    const float *int_box, *leaf_box;
-    uint2 *q[2];
-    uint32_t *ring;
-    void *nodes;
-    uint32_t *parents, *levels;
+    CollapseArgs a;
 };
 constexpr int kRingWords = 2 * kCollapseRing + 1;  // what the host reads after a batch
 
@@ -2705,14 +2808,15 @@ template <int W>
 void collapse_batch(const CollapseState &c, hipStream_t st) {
     uint64_t bound = c.known;
     for (int j = 0; j < c.batch; ++j) {
-        unsigned blocks = rg_blocks((int64_t)(bound ? bound : 1), kThreads);
-        if (blocks > 1024) blocks = 1024;
         const int level = c.d + j;
-        k_collapse<W><<<blocks, kThreads, 0, st>>>(c.wch, c.wlink, c.winner, c.int_box, c.leaf_box, c.q[level & 1],
-                                                    c.q[(level + 1) & 1], c.ring, level,
-                                                    reinterpret_cast<RgNode<W> *>(c.nodes), c.parents, c.levels,
-                                                    c.cap);
-        bound = std::min<uint64_t>((uint64_t)c.cap, bound * (uint64_t)W);
+        if (level == 0) {
+            k_collapse_top<W><<<1, kCollapseTop, 0, st>>>(c.a);
+        } else if (level >= collapse_top(W)) {
+            unsigned blocks = rg_blocks((int64_t)(bound ? bound : 1), kCollapseT);
+            if (blocks > 512) blocks = 512;
+            k_collapse<W><<<blocks, kCollapseT, 0, st>>>(c.a, level);
+        }
+        bound = std::min<uint64_t>((uint64_t)c.a.cap, bound * (uint64_t)W);
     }
 }
 
@@ -2739,7 +2843,7 @@ rg_status collapse_absorb(CollapseState &c, const uint32_t *hr) {
     }
     c.d += c.batch;
     c.batch = kCollapseBatch;
-    if (c.d > 4096 || c.n_nodes > c.cap) return RG_ERR_HIP;  // never expected
+    if (c.d > 4096 || c.n_nodes > c.a.cap) return RG_ERR_HIP;  // never expected
     return RG_OK;
 }
 
@@ -2762,24 +2866,13 @@ rg_status collapse_begin(const LbvhScratch &s, int64_t n, int leaf_max, void *no
         c.depth = 1;
         return RG_OK;
     }
-    c.cap = (uint32_t)(n - 1);
-    c.wch = s.wch;
-    c.wlink = s.wlink;
-    c.winner = s.winner;
-    c.int_box = s.int_box;
-    c.leaf_box = s.leaf_box;
-    c.q[0] = s.q0;
-    c.q[1] = s.q1;
-    c.ring = s.qcount;
-    c.nodes = nodes;
-    c.parents = parents;
-    c.levels = levels;
+    c.a = {s.wch, s.wlink, s.winner, s.int_box, s.leaf_box, {s.q0, s.q1}, s.qcount, nodes, parents, levels,
+           (uint32_t)(n - 1)};
     k_wide_plan<W><<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(s.left, s.right, s.first, s.last, s.int_box,
                                                                      leaf_max, n - 1, s.wch, s.wlink, s.winner);
-    k_collapse_init<<<1, 1, 0, st>>>(s.q0, c.ring, parents, levels);
     RG_LAUNCH_CHECK();
     const int b = (int)std::ceil(1.6 * std::log((double)n) / std::log((double)W)) + 2;
-    c.batch = std::max(kCollapseBatch, std::min(kCollapseFirstMax, b));
+    c.batch = std::max({kCollapseBatch, collapse_top(W), std::min(kCollapseFirstMax, b)});
     return collapse_launch(c, st);
 }
 
@@ -2787,7 +2880,7 @@ rg_status collapse_begin(const LbvhScratch &s, int64_t n, int leaf_max, void *no
 // on until the depth is known; waits for `st` at each read.
 rg_status collapse_finish(CollapseState &c, hipStream_t st, uint32_t *hr) {
     while (c.depth == 0) {
-        RG_HIP(hipMemcpyAsync(hr, c.ring, kRingWords * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+        RG_HIP(hipMemcpyAsync(hr, c.a.ring, kRingWords * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         RG_HIP(hipStreamSynchronize(st));
         rg_status r = collapse_absorb(c, hr);
         if (r != RG_OK) return r;
@@ -2959,7 +3052,7 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
         else r = collapse_begin<8>(s, n, leaf_max, nodes, parents, levels, st, c);
         if (r != RG_OK) return r;
         if (c.depth == 0)
-            RG_HIP(hipMemcpyAsync(out->coll_hr, c.ring, kRingWords * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+            RG_HIP(hipMemcpyAsync(out->coll_hr, c.a.ring, kRingWords * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     } else if (nodes) {
         if (width == 2) r = collapse<2>(s, n, leaf_max, nodes, parents, levels, st, &out->depth, &out->n_nodes);
         else if (width == 4) r = collapse<4>(s, n, leaf_max, nodes, parents, levels, st, &out->depth, &out->n_nodes);
