@@ -122,15 +122,16 @@ __global__ void k_tri_boxes(const float *__restrict__ verts, int64_t n_verts,
 
 // Bounds of the box centres c = 0.5 (lo + hi): one partial per block,
 // part[6 b .. 6 b + 5] = min xyz, max xyz (k_morton reduces them, so no
-// atomics and no initialised bounds are needed).  Also clears zero[0, nz):
-// the sort's digit counts, tickets and tile status words.
+// atomics and no initialised bounds are needed).  Also clears zero[0, nz)
+// and zero2[0, nz2): the sort's digit counts.
 constexpr int kBoundParts = 512;  // largest grid of k_centre_bounds
 __global__ void __launch_bounds__(kThreads) k_centre_bounds(const float *__restrict__ box, int64_t n,
                                                             float *__restrict__ part, uint32_t *__restrict__ zero,
-                                                            int64_t nz) {
+                                                            int64_t nz, uint32_t *__restrict__ zero2, int64_t nz2) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     for (int64_t j = i0; j < nz; j += stride) zero[j] = 0u;
+    for (int64_t j = i0; j < nz2; j += stride) zero2[j] = 0u;
     float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
 #pragma unroll 4
     for (int64_t i = i0; i < n; i += stride) {
@@ -203,15 +204,33 @@ __device__ inline uint64_t morton_key(const float *__restrict__ b, const uint32_
     return morton_key(b, lo, hi);
 }
 
-// Keys and ids of one tile of kSortTile boxes per block, and the counts of
-// every 8-bit digit of the keys for all eight sort passes, added into
-// count[copy][pass][digit] (copy = block mod kCountCopies; cleared by
-// k_centre_bounds).  The centre bounds are the reduction of
-// k_centre_bounds' nparts partials.
+// Where the tiles' digit counts of a radix sort pass go (below): cnt[tile]
+// [digit], and added into group[tile / kSortGroup][digit] if there is more than
+// one group; with groups = 0 cnt[digit][tile] alone.
+constexpr int kSortGroup = 16;
+struct TileCounts {
+    uint32_t *cnt, *group;  // group: one pass's (cleared by k_centre_bounds)
+    int nb, groups;
+};
+
+__device__ inline void put_tile_count(const TileCounts &T, int tile, int digit, uint32_t c) {
+    if (T.groups) {
+        T.cnt[(int64_t)tile * 256 + digit] = c;
+        if (c && T.groups > 1) atomicAdd(&T.group[(tile / kSortGroup) * 256 + digit], c);
+    } else {
+        T.cnt[(int64_t)digit * T.nb + tile] = c;
+    }
+}
+
+// Keys and ids of one tile of kSortTile boxes per block, the tile's digit
+// counts for the first sort pass, and the counts of every 8-bit digit of the
+// keys for all eight sort passes, added into count[copy][pass][digit] (copy =
+// block mod kCountCopies; cleared by k_centre_bounds).  The centre bounds are
+// the reduction of k_centre_bounds' nparts partials.
 __global__ void __launch_bounds__(kSortThreads) k_morton(const float *__restrict__ box, int64_t n,
                                                          const float *__restrict__ part, int nparts, int key_shift,
                                                          uint64_t *__restrict__ keys, uint32_t *__restrict__ ids,
-                                                         uint32_t *__restrict__ count) {
+                                                         uint32_t *__restrict__ count, TileCounts T) {
     constexpr int kWaves = kSortThreads / 64;
     __shared__ uint32_t h[8 * 256];
     __shared__ float red[6][kWaves];
@@ -281,19 +300,25 @@ __global__ void __launch_bounds__(kSortThreads) k_morton(const float *__restrict
     for (int j = t; j < 8 * 256; j += kSortThreads) {
         const uint32_t c = h[j];
         if (c) atomicAdd(&cc[j], c);
+        if (j < 256) put_tile_count(T, (int)blockIdx.x, j, c);
     }
 }
 
 // -------------------------------------------------- 3. LSD radix sort
-// Three launches per pass of 8 bits, each spread over every compute unit
-// (a unit keeps only so many loads in flight, so a tile of 2,048 keys per
-// workgroup): the digit counts of every tile (k_sort_count, digit-major),
-// their exclusive scan per digit plus the pass's count of all smaller
-// digits (k_sort_scan, one workgroup per digit; the totals of every pass
-// were counted with the keys), and the stable scatter (k_sort_scatter).  A
-// single launch per pass with a look-back over earlier tiles' counts was
-// slower here: with ~300 tiles finishing at once its chain of cross-die
-// reads outlasts the two extra launches.
+// Two launches per pass of 8 bits, each spread over every compute unit (a
+// unit keeps only so many loads in flight, so a tile of 2,048 keys per
+// workgroup): the digit counts of every tile (k_sort_count; the first pass's
+// come with the keys, as do the totals of every pass) and the stable scatter
+// (k_sort_scatter).  A tile's first position per digit is the pass's count of
+// all smaller digits plus the counts of the tiles before it: the scatter adds
+// them up itself, over whole groups of kSortGroup tiles and the tiles of its
+// own group, up to kSortDirect tiles -- 79 rows of 256 counts at most, which
+// arrive together.  Beyond that the rows would outweigh the keys, and a third
+// launch scans the counts (k_sort_scan, one workgroup per digit), 4 us each at
+// 627,200 keys.  A single launch per pass with a look-back over earlier tiles'
+// counts was slower here: with ~300 tiles finishing at once its chain of
+// cross-die reads outlasts the extra launches.
+constexpr int kSortDirect = 1024;
 
 // Ranks a tile's items by digit, tile order = (wave, item, lane): rk[k] =
 // count of equal digits before item k within its wave; wcnt[w][d] (zero on
@@ -342,27 +367,32 @@ __device__ inline int load_tile(const K *__restrict__ keys, int64_t n, K (&key)[
     return in_tile;
 }
 
-// cnt[d * nb + tile] = the tile's count of digit d.
+// A tile's digit counts.
 template <typename K>
 __global__ void __launch_bounds__(kSortThreads) k_sort_count(const K *__restrict__ keys, int64_t n, int shift,
-                                                             uint32_t *__restrict__ cnt, int nb) {
-    constexpr int kWaves = kSortThreads / 64;
+                                                             TileCounts T) {
     static_assert(kSortThreads >= 256, "a thread per digit");
-    __shared__ uint32_t wcnt[kWaves][256];
-    const int t = threadIdx.x;
-    for (int j = t; j < kWaves * 256; j += kSortThreads) (&wcnt[0][0])[j] = 0u;
+    __shared__ uint32_t h[256];
+    const int t = threadIdx.x, lane = t & 63;
+    constexpr int kPerWave = kSortTile / (kSortThreads / 64);
+    if (t < 256) h[t] = 0u;
     K key[kSortItems];
-    uint32_t rk[kSortItems];
     const int in_tile = load_tile(keys, n, key);
     __syncthreads();
-    rank_items(key, in_tile, shift, rk, wcnt);
-    __syncthreads();
-    if (t < 256) {
-        uint32_t tot = 0u;
 #pragma unroll
-        for (int q = 0; q < kWaves; ++q) tot += wcnt[q][t];
-        cnt[(int64_t)t * nb + blockIdx.x] = tot;
+    for (int k = 0; k < kSortItems; ++k) {
+        const bool valid = (t >> 6) * kPerWave + k * 64 + lane < in_tile;
+        const uint32_t d = (uint32_t)(key[k] >> shift) & 255u;
+        const uint64_t vm = __ballot(valid);
+        const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);  // lane 0: valid whenever vm != 0
+        if (__ballot(valid && d != d0) == 0ull) {  // one digit across the wave (the high digits)
+            if (lane == 0 && vm) atomicAdd(&h[d0], (uint32_t)__popcll(vm));
+        } else if (valid) {
+            atomicAdd(&h[d], 1u);
+        }
     }
+    __syncthreads();
+    if (t < 256) put_tile_count(T, (int)blockIdx.x, t, h[t]);
 }
 
 // Exclusive scan in place.  A block scans a chunk of kScanChunk elements at
@@ -448,23 +478,44 @@ __global__ void __launch_bounds__(kScanThreads) k_sort_scan(uint32_t *cnt, int n
 
 // Stable scatter of tile blockIdx.x: its keys ranked by digit, put in digit
 // order in LDS, then written out with consecutive threads on consecutive
-// positions of each digit's run, from the tile's first position per digit
-// in goff[d * nb + tile].
+// positions of each digit's run, from the tile's first position per digit:
+// scanned in T.cnt[d * nb + tile], or added up here (T.groups != 0; total: the
+// pass's digit counts, kCountCopies copies 2,048 words apart).
 template <typename K>
 __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(const K *__restrict__ keys_in,
                                                                const uint32_t *__restrict__ ids_in,
                                                                K *__restrict__ keys_out,
                                                                uint32_t *__restrict__ ids_out, int64_t n, int shift,
-                                                               const uint32_t *__restrict__ goff, int nb) {
+                                                               TileCounts T, const uint32_t *__restrict__ total) {
     constexpr int kWaves = kSortThreads / 64, kPerWave = kSortTile / kWaves;
     __shared__ K skey[kSortTile];
     __shared__ uint32_t sid[kSortTile];
     __shared__ uint32_t wcnt[kWaves][256];  // per wave: digit counts, then offsets within the tile's digit
-    __shared__ uint32_t dstart[256], gpos[256];
-    __shared__ uint32_t wsum[kWaves];
+    __shared__ uint32_t dstart[256], gpos[256], tsum[256];
+    __shared__ uint32_t wsum[kWaves], wwhole[kWaves];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int j = t; j < kWaves * 256; j += kSortThreads) (&wcnt[0][0])[j] = 0u;
-    if (t < 256) gpos[t] = goff[(int64_t)t * nb + blockIdx.x];
+    // threads 0 .. 255: digit t's count in the groups before, and the totals;
+    // the next 256: its count in the tiles before within the group
+    static_assert(kSortThreads == 512, "two threads per digit");
+    uint32_t before = 0u, whole = 0u;
+    if (T.groups) {
+        const int g = (int)blockIdx.x / kSortGroup, d = t & 255;
+        if (t < 256) {
+#pragma unroll
+            for (int c = 0; c < kCountCopies; ++c) whole += total[2048 * c + d];
+#pragma unroll 8
+            for (int q = 0; q < g; ++q) before += T.group[q * 256 + d];
+        } else {
+            const uint32_t *row = T.cnt + (int64_t)g * kSortGroup * 256 + d;
+            const int m = (int)blockIdx.x % kSortGroup;
+#pragma unroll
+            for (int q = 0; q < kSortGroup - 1; ++q) before += q < m ? row[q * 256] : 0u;
+            tsum[d] = before;
+        }
+    } else if (t < 256) {
+        gpos[t] = T.cnt[(int64_t)t * T.nb + blockIdx.x];
+    }
     K key[kSortItems];
     uint32_t id[kSortItems], rk[kSortItems];
     const int in_tile = load_tile(keys_in, n, key);
@@ -482,17 +533,30 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(const K *__restri
             tot += c;
         }
     }
-    uint32_t x = tot;
+    // exclusive sums over the digits: of the tile's counts, and of the pass's
+    uint32_t x = tot, z = whole;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+        const uint32_t y = __shfl_up(x, o, 64), v = __shfl_up(z, o, 64);
+        if (lane >= o) {
+            x += y;
+            z += v;
+        }
     }
-    if (lane == 63) wsum[w] = x;
+    if (lane == 63) {
+        wsum[w] = x;
+        wwhole[w] = z;
+    }
     __syncthreads();
-    uint32_t pre = 0u;
-    for (int q = 0; q < w; ++q) pre += wsum[q];
-    if (t < 256) dstart[t] = pre + x - tot;
+    uint32_t pre = 0u, low = 0u;
+    for (int q = 0; q < w; ++q) {
+        pre += wsum[q];
+        low += wwhole[q];
+    }
+    if (t < 256) {
+        dstart[t] = pre + x - tot;
+        if (T.groups) gpos[t] = low + z - whole + before + tsum[t];
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
@@ -2989,19 +3053,28 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
     // digit counts of every pass, then one launch per pass
     int64_t bparts = (n + kThreads - 1) / kThreads;
     if (bparts > kBoundParts) bparts = kBoundParts;
-    k_centre_bounds<<<(unsigned)bparts, kThreads, 0, st>>>(prim_box, n, s.part, s.sortz, s.sortz_words);
+    // the group counts of all passes lie where the wide-node plan goes later
+    const int passes = out->key_shift ? 4 : 8;
+    const int groups = nblocks <= kSortDirect ? (nblocks + kSortGroup - 1) / kSortGroup : 0;
+    const int64_t group_words = groups > 1 ? (int64_t)passes * groups * 256 : 0;  // at most 4 n words
+    static_assert(8 * 256 * 2 <= 8 * kSortGroup * kSortTile, "two groups' counts fit the plan of their tiles");
+    auto counts = [&](int p) {
+        return TileCounts{s.cnt, (uint32_t *)s.wch + (int64_t)p * groups * 256, nblocks, groups};
+    };
+    k_centre_bounds<<<(unsigned)bparts, kThreads, 0, st>>>(prim_box, n, s.part, s.sortz, s.sortz_words,
+                                                           (uint32_t *)s.wch, group_words);
     RG_LAUNCH_CHECK();
     k_morton<<<nblocks, kSortThreads, 0, st>>>(prim_box, n, s.part, (int)bparts, out->key_shift, s.keys, s.ids,
-                                               s.count);
+                                               s.count, counts(0));
     RG_LAUNCH_CHECK();
     // 8 passes of 8 bits (4 for 30-bit keys); the result lands in ka / ia
     uint64_t *ka = s.keys, *kb = s.keys2;
     uint32_t *ia = s.ids, *ib = s.ids2;
-    const int passes = out->key_shift ? 4 : 8;
     for (int p = 0; p < passes; ++p) {
-        k_sort_count<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, n, 8 * p, s.cnt, nblocks);
-        k_sort_scan<<<256, kScanThreads, 0, st>>>(s.cnt, nblocks, s.count + 256 * p);
-        k_sort_scatter<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, ia, kb, ib, n, 8 * p, s.cnt, nblocks);
+        const TileCounts T = counts(p);
+        if (p > 0) k_sort_count<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, n, 8 * p, T);
+        if (!groups) k_sort_scan<<<256, kScanThreads, 0, st>>>(s.cnt, nblocks, s.count + 256 * p);
+        k_sort_scatter<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, ia, kb, ib, n, 8 * p, T, s.count + 256 * p);
         RG_LAUNCH_CHECK();
         uint64_t *tk = ka; ka = kb; kb = tk;
         uint32_t *ti = ia; ia = ib; ib = ti;
