@@ -644,8 +644,7 @@ __global__ void k_karras(const uint64_t *__restrict__ keys, int64_t n, int32_t *
 }
 
 // -------------------------------------------------------- 5. box refit
-// Inner boxes come from the leaf ranges (k_range_* below), after
-// k_leaf_boxes has gathered the leaf boxes in leaf order.
+// Inner boxes come from the leaf ranges (k_range_* below).
 
 // --------------------------------------------------- 6. wide collapse
 __device__ inline float surface_area(const float *b) {
@@ -1930,15 +1929,6 @@ __global__ void __launch_bounds__(1024) k_sizes_top(const int32_t *__restrict__ 
     }
 }
 
-__global__ void k_leaf_boxes(const float *__restrict__ prim_box, const uint32_t *__restrict__ ids, int64_t n,
-                             float *__restrict__ leaf_box) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t src = ids[i];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) leaf_box[6 * i + k] = prim_box[6 * (int64_t)src + k];
-}
-
 // ---------------------------------------------- inner boxes from ranges
 // Every inner node of the radix tree covers a contiguous range of leaves
 // (first .. last, leaf order), and its box is the union of their boxes.  The
@@ -1959,16 +1949,23 @@ __device__ inline void box_union(float u[6], const float *__restrict__ b) {
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_range_blocks(const float *__restrict__ leaf_box, int64_t n,
-                                                           float *__restrict__ pre, float *__restrict__ suf,
-                                                           float *__restrict__ table) {
+// The leaf boxes are gathered into leaf order on the way; without tables
+// (pre null: one primitive) that is all.
+__global__ void __launch_bounds__(kThreads) k_range_blocks(const float *__restrict__ prim_box,
+                                                           const uint32_t *__restrict__ ids, int64_t n,
+                                                           float *__restrict__ leaf_box, float *__restrict__ pre,
+                                                           float *__restrict__ suf, float *__restrict__ table) {
     __shared__ float b[kThreads * 6];
     const int t = threadIdx.x;
     const int64_t i = blockIdx.x * (int64_t)kThreads + t;
+    const int64_t src = i < n ? (int64_t)ids[i] : 0;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) b[6 * t + k] = i < n ? leaf_box[6 * i + k] : (k < 3 ? INFINITY : -INFINITY);
+    for (int k = 0; k < 6; ++k) b[6 * t + k] = i < n ? prim_box[6 * src + k] : (k < 3 ? INFINITY : -INFINITY);
     __syncthreads();
     if (i >= n) return;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) leaf_box[6 * i + k] = b[6 * t + k];
+    if (!pre) return;
     const int g0 = t & ~(kRangeLeaves - 1), r = t & (kRangeLeaves - 1);
     float p[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
     float q[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -3003,7 +3000,7 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
                         int32_t radius, void *nodes, uint32_t *parents, uint32_t *levels, RgArena &arena,
                         hipStream_t st, RgLbvhOut *out, bool keep_stages, uint64_t *keys_out, int32_t *left_out,
                         int32_t *right_out, float *boxes_out) {
-    LbvhScratch s;
+    LbvhScratch s{};
     if (!carve(arena, n, builder, s)) return RG_ERR_OUT_OF_MEMORY;
     if (builder == RG_BUILDER_LBVH && n <= kSmallMax) {
         // the whole build in one workgroup, one host wait for its summary
@@ -3113,11 +3110,13 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
                                                                       s.first, s.last);
             RG_LAUNCH_CHECK();
         }
-        k_leaf_boxes<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(prim_box, ia, n, s.leaf_box);
+        // (the clustering builder carves no tables, and comes here with n = 1)
+        k_range_blocks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(prim_box, ia, n, s.leaf_box,
+                                                                     n > 1 ? s.pre : nullptr, n > 1 ? s.suf : nullptr,
+                                                                     n > 1 ? s.rtab : nullptr);
         RG_LAUNCH_CHECK();
         if (n > 1) {  // inner boxes from the leaf ranges: no host step
             const int64_t nbr = (n + kRangeLeaves - 1) / kRangeLeaves;
-            k_range_blocks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(s.leaf_box, n, s.pre, s.suf, s.rtab);
             const int top = (int)range_levels(nbr) - 1;
             for (int j0 = 0; j0 < top; j0 += kRangeStride)
                 k_range_levels<<<rg_blocks(kRangeStride * nbr, kThreads), kThreads, 0, st>>>(s.rtab, nbr, j0, top);
