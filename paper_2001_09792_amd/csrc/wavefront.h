@@ -38,12 +38,17 @@ struct RgJobDev {
     uint32_t *gbuf;  // nullable: the material each primary ray shaded (RG_MISS: sky)
 };
 
+// Counters of the ray queue of passes of a parity and of the shadow queue in
+// passes of a parity: what pass p appends to -- its shadow rays, the rays of
+// pass p + 1 -- lies side by side, 8-byte aligned, for one add.
+__host__ __device__ constexpr int rg_count_shadow(int64_t pass) { return 2 * (int)(pass & 1); }
+__host__ __device__ constexpr int rg_count_rays(int64_t pass) { return 2 * (int)((pass + 1) & 1) + 1; }
+
 // Device buffers of a wavefront render, carved from one caller buffer:
-// accumulators (3 x u64 per pixel), statistics, counters (0, 1: entries of the
-// two ray queues; 2, 3: of the shadow queue in passes of either parity; 4: the
-// first entry reserved for a frame's camera rays; 5, 6: rays and shadow rays
-// of the last pass), frame / top-level / material tables,
-// hit arrays, two ray queues and a shadow queue of `cap` entries each.
+// accumulators (3 x u64 per pixel), statistics, counters (0 .. 3: entries of
+// the queues, below; 4: the first entry reserved for a frame's camera rays; 5,
+// 6: rays and shadow rays of the last pass), frame / top-level / material
+// tables, hit arrays, two ray queues and a shadow queue of `cap` entries each.
 struct RgWaveBufs {
     unsigned long long *acc, *stat;
     uint32_t *counts;
