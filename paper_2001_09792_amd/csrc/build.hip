@@ -1118,6 +1118,7 @@ struct SmallArgs {
     const float *prim_box;
     int32_t n, leaf_max;
     uint64_t *keys_out;             // sorted keys (nullable: only for the stage check)
+    bool tree_out;                  // the binary tree is wanted in the arrays below, also where it is built in LDS
     uint32_t *ids;                  // sorted primitive order
     int32_t *left, *right, *pint, *pleaf, *first, *last;
     float *int_box, *leaf_box;
@@ -1368,13 +1369,15 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_build(SmallArgs a) {
             if (done[0][0] & 1u) break;  // the root
         }
     }
-    if (RESIDENT && a.keys_out) {  // the stage check reads the binary tree from the scratch arrays
+    if (RESIDENT && a.tree_out) {
         for (int i = t; i < n - 1; i += kSmallThreads) {
             a.left[i] = left[i];
             a.right[i] = right[i];
+            a.pint[i] = pint[i];
 #pragma unroll
             for (int q = 0; q < 6; ++q) a.int_box[6 * i + q] = int_box[6 * i + q];
         }
+        if (t < n) a.pleaf[t] = pleaf[t];
     }
     const float *root = n > 1 ? int_box : lbox;
     if (t == 0) {
@@ -3007,9 +3010,9 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
                         int32_t *right_out, float *boxes_out) {
     LbvhScratch s{};
     if (!carve(arena, n, builder, s)) return RG_ERR_OUT_OF_MEMORY;
-    if (builder == RG_BUILDER_LBVH && n <= kSmallMax) {
-        // the whole build in one workgroup, one host wait for its summary
-        SmallArgs sa;
+    // a build in one workgroup: the whole of it, or (no nodes) the binary tree
+    auto small_args = [&](void *nd, uint32_t *par, uint32_t *lev) {
+        SmallArgs sa{};
         sa.prim_box = prim_box;
         sa.n = (int32_t)n;
         sa.leaf_max = leaf_max;
@@ -3021,12 +3024,18 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
         sa.leaf_box = s.leaf_box;
         sa.q[0] = s.q0;
         sa.q[1] = s.q1;
-        sa.nodes = nodes;
-        sa.parents = parents;
-        sa.levels = levels;
-        sa.flag_in = out->flag_in;
+        sa.nodes = nd;
+        sa.parents = par;
+        sa.levels = lev;
         sa.key_shift = out->key_shift;
         sa.res = s.small;
+        return sa;
+    };
+    if (builder == RG_BUILDER_LBVH && n <= kSmallMax) {
+        // the whole build in one workgroup, one host wait for its summary
+        SmallArgs sa = small_args(nodes, parents, levels);
+        sa.tree_out = keep_stages;
+        sa.flag_in = out->flag_in;
         const size_t lds = small_lds_bytes(n);
         const TlasFuse *fuse = reinterpret_cast<const TlasFuse *>(out->tlas_fuse);
         if (fuse && n <= kResidentMax) {
@@ -3074,69 +3083,77 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
         out->deferred = nullptr;
         return r;
     }
-    const int nblocks = (int)((n + kSortTile - 1) / kSortTile);
-    // centre bounds (partials; the sort's counters cleared), keys with the
-    // digit counts of every pass, then one launch per pass
-    int64_t bparts = (n + kThreads - 1) / kThreads;
-    if (bparts > kBoundParts) bparts = kBoundParts;
-    // the group counts of all passes lie where the wide-node plan goes later
-    const int passes = out->key_shift ? 4 : 8;
-    const int groups = nblocks <= kSortDirect ? (nblocks + kSortGroup - 1) / kSortGroup : 0;
-    const int64_t group_words = groups > 1 ? (int64_t)passes * groups * 256 : 0;  // at most 4 n words
-    static_assert(8 * 256 * 2 <= 8 * kSortGroup * kSortTile, "two groups' counts fit the plan of their tiles");
-    auto counts = [&](int p) {
-        return TileCounts{s.cnt, (uint32_t *)s.wch + (int64_t)p * groups * 256, nblocks, groups};
-    };
-    k_centre_bounds<<<(unsigned)bparts, kThreads, 0, st>>>(prim_box, n, s.part, s.sortz, s.sortz_words,
-                                                           (uint32_t *)s.wch, group_words);
-    RG_LAUNCH_CHECK();
-    k_morton<<<nblocks, kSortThreads, 0, st>>>(prim_box, n, s.part, (int)bparts, out->key_shift, s.keys, s.ids,
-                                               s.count, counts(0));
-    RG_LAUNCH_CHECK();
-    // 8 passes of 8 bits (4 for 30-bit keys); the result lands in ka / ia
     uint64_t *ka = s.keys, *kb = s.keys2;
     uint32_t *ia = s.ids, *ib = s.ids2;
-    for (int p = 0; p < passes; ++p) {
-        const TileCounts T = counts(p);
-        if (p > 0) k_sort_count<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, n, 8 * p, T);
-        if (!groups) k_sort_scan<<<256, kScanThreads, 0, st>>>(s.cnt, nblocks, s.count + 256 * p);
-        k_sort_scatter<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, ia, kb, ib, n, 8 * p, T, s.count + 256 * p);
+    if (builder == RG_BUILDER_TREELET && n > 1 && n <= kResidentMax) {
+        // the tree that the rounds restructure in one workgroup: 13 to 60 us,
+        // where the launches below take 150 for 64 primitives as for 1,024
+        SmallArgs sa = small_args(nullptr, nullptr, nullptr);
+        sa.tree_out = true;
+        k_small_build<2, true><<<1, kSmallThreads, small_lds_bytes(n), st>>>(sa);
         RG_LAUNCH_CHECK();
-        uint64_t *tk = ka; ka = kb; kb = tk;
-        uint32_t *ti = ia; ia = ib; ib = ti;
+    } else {
+        const int nblocks = (int)((n + kSortTile - 1) / kSortTile);
+        // centre bounds (partials; the sort's counters cleared), keys with the
+        // digit counts of every pass, then one launch per pass
+        int64_t bparts = (n + kThreads - 1) / kThreads;
+        if (bparts > kBoundParts) bparts = kBoundParts;
+        // the group counts of all passes lie where the wide-node plan goes later
+        const int passes = out->key_shift ? 4 : 8;
+        const int groups = nblocks <= kSortDirect ? (nblocks + kSortGroup - 1) / kSortGroup : 0;
+        const int64_t group_words = groups > 1 ? (int64_t)passes * groups * 256 : 0;  // at most 4 n words
+        static_assert(8 * 256 * 2 <= 8 * kSortGroup * kSortTile, "two groups' counts fit the plan of their tiles");
+        auto counts = [&](int p) {
+            return TileCounts{s.cnt, (uint32_t *)s.wch + (int64_t)p * groups * 256, nblocks, groups};
+        };
+        k_centre_bounds<<<(unsigned)bparts, kThreads, 0, st>>>(prim_box, n, s.part, s.sortz, s.sortz_words,
+                                                               (uint32_t *)s.wch, group_words);
+        RG_LAUNCH_CHECK();
+        k_morton<<<nblocks, kSortThreads, 0, st>>>(prim_box, n, s.part, (int)bparts, out->key_shift, s.keys, s.ids,
+                                                   s.count, counts(0));
+        RG_LAUNCH_CHECK();
+        // 8 passes of 8 bits (4 for 30-bit keys); the result lands in ka / ia
+        for (int p = 0; p < passes; ++p) {
+            const TileCounts T = counts(p);
+            if (p > 0) k_sort_count<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, n, 8 * p, T);
+            if (!groups) k_sort_scan<<<256, kScanThreads, 0, st>>>(s.cnt, nblocks, s.count + 256 * p);
+            k_sort_scatter<uint64_t><<<nblocks, kSortThreads, 0, st>>>(ka, ia, kb, ib, n, 8 * p, T, s.count + 256 * p);
+            RG_LAUNCH_CHECK();
+            uint64_t *tk = ka; ka = kb; kb = tk;
+            uint32_t *ti = ia; ia = ib; ib = ti;
+        }
+        if (builder != RG_BUILDER_PLOC || n == 1) {
+            if (n > 1) {
+                k_karras<<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(ka, n, s.left, s.right, s.pint, s.pleaf,
+                                                                          s.first, s.last);
+                RG_LAUNCH_CHECK();
+            }
+            // (the clustering builder carves no tables, and comes here with n = 1)
+            k_range_blocks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(prim_box, ia, n, s.leaf_box,
+                                                                         n > 1 ? s.pre : nullptr, n > 1 ? s.suf : nullptr,
+                                                                         n > 1 ? s.rtab : nullptr);
+            RG_LAUNCH_CHECK();
+            if (n > 1) {  // inner boxes from the leaf ranges: no host step
+                const int64_t nbr = (n + kRangeLeaves - 1) / kRangeLeaves;
+                const int top = (int)range_levels(nbr) - 1;
+                for (int j0 = 0; j0 < top; j0 += kRangeStride)
+                    k_range_levels<<<rg_blocks(kRangeStride * nbr, kThreads), kThreads, 0, st>>>(s.rtab, nbr, j0, top);
+                k_range_boxes<<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(s.first, s.last, n - 1, s.leaf_box,
+                                                                                s.pre, s.suf, s.rtab, nbr, s.int_box);
+                RG_LAUNCH_CHECK();
+            }
+        }
     }
-    if (builder == RG_BUILDER_PLOC && n > 1) {
-        rg_status r = ploc_build(prim_box, n, radius, ia, ib, s, st);
+    if (n > 1 && builder != RG_BUILDER_LBVH) {
+        rg_status r = builder == RG_BUILDER_PLOC ? ploc_build(prim_box, n, radius, ia, ib, s, st)
+                                                 : treelet_build(n, radius, ia, ib, s, st);
         if (r != RG_OK) return r;
         ia = ib;
-    } else {
-        if (n > 1) {
-            k_karras<<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(ka, n, s.left, s.right, s.pint, s.pleaf,
-                                                                      s.first, s.last);
-            RG_LAUNCH_CHECK();
-        }
-        // (the clustering builder carves no tables, and comes here with n = 1)
-        k_range_blocks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(prim_box, ia, n, s.leaf_box,
-                                                                     n > 1 ? s.pre : nullptr, n > 1 ? s.suf : nullptr,
-                                                                     n > 1 ? s.rtab : nullptr);
-        RG_LAUNCH_CHECK();
-        if (n > 1) {  // inner boxes from the leaf ranges: no host step
-            const int64_t nbr = (n + kRangeLeaves - 1) / kRangeLeaves;
-            const int top = (int)range_levels(nbr) - 1;
-            for (int j0 = 0; j0 < top; j0 += kRangeStride)
-                k_range_levels<<<rg_blocks(kRangeStride * nbr, kThreads), kThreads, 0, st>>>(s.rtab, nbr, j0, top);
-            k_range_boxes<<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(s.first, s.last, n - 1, s.leaf_box,
-                                                                            s.pre, s.suf, s.rtab, nbr, s.int_box);
-            RG_LAUNCH_CHECK();
-        }
-        if (builder == RG_BUILDER_TREELET && n > 1) {
-            rg_status r = treelet_build(n, radius, ia, ib, s, st);
-            if (r != RG_OK) return r;
-            ia = ib;
-        }
     }
     if (keep_stages) {
-        RG_HIP(hipMemcpyAsync(keys_out, ka, 8 * n, hipMemcpyDeviceToDevice, st));
+        // (the one-workgroup tree has written them)
+        if (builder != RG_BUILDER_TREELET || n == 1 || n > kResidentMax)
+            RG_HIP(hipMemcpyAsync(keys_out, ka, 8 * n, hipMemcpyDeviceToDevice, st));
         if (n > 1) {
             RG_HIP(hipMemcpyAsync(left_out, s.left, 4 * (n - 1), hipMemcpyDeviceToDevice, st));
             RG_HIP(hipMemcpyAsync(right_out, s.right, 4 * (n - 1), hipMemcpyDeviceToDevice, st));
