@@ -1121,6 +1121,7 @@ struct SmallArgs {
     bool tree_out;                  // the binary tree is wanted in the arrays below, also where it is built in LDS
     uint32_t *ids;                  // sorted primitive order
     int32_t *left, *right, *pint, *pleaf, *first, *last;
+    int32_t *size;                  // nullable: leaves below each inner node, with tree_out
     float *int_box, *leaf_box;
     uint2 *q[2];
     void *nodes;                    // nullable: binary hierarchy only
@@ -1374,6 +1375,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_build(SmallArgs a) {
             a.left[i] = left[i];
             a.right[i] = right[i];
             a.pint[i] = pint[i];
+            if (a.size) a.size[i] = last[i] - first[i] + 1;
 #pragma unroll
             for (int q = 0; q < 6; ++q) a.int_box[6 * i + q] = int_box[6 * i + q];
         }
@@ -1754,7 +1756,9 @@ __global__ void k_ploc_relabel(int64_t n, int32_t *__restrict__ left, int32_t *_
 // no fused multiply-add, splits holding the subset's lowest leaf tried in
 // increasing bit order, the first minimum kept); the node keeps its index and
 // the other inner nodes take the opened nodes' indices, ascending, in
-// pre-order (left subtree first).
+// pre-order (left subtree first).  The counts of leaves below each inner node
+// are kept up on the way, so that the leaves can be renumbered afterwards
+// without another order by depth.
 constexpr int kTreelet = 7;
 constexpr int kTreeletMaxRounds = 8;
 
@@ -2011,10 +2015,11 @@ __global__ void k_range_levels(float *table, int64_t nb, int j0, int top) {
 __global__ void k_range_boxes(const int32_t *__restrict__ first, const int32_t *__restrict__ last, int64_t m,
                               const float *__restrict__ leaf_box, const float *__restrict__ pre,
                               const float *__restrict__ suf, const float *__restrict__ table, int64_t nb,
-                              float *__restrict__ int_box) {
+                              float *__restrict__ int_box, int32_t *__restrict__ size) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= m) return;
     const int32_t f = first[i], l = last[i];
+    if (size) size[i] = l - f + 1;  // leaves below, kept up by the treelet rounds
     const int32_t bf = f / kRangeLeaves, bl = l / kRangeLeaves;
     float u[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
     if (bf == bl) {
@@ -2106,8 +2111,9 @@ __device__ __forceinline__ void treelet_level(TreeletShared &sh, const uint32_t 
 // but of the node and the nodes below it, and of parents' links to the node's
 // descendants.
 __device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *left, int32_t *right, int32_t *parent_int,
-                                    int32_t *parent_leaf, float *int_box, const float *__restrict__ leaf_box,
-                                    TreeletShared &sh, int lane) {
+                                             int32_t *parent_leaf, float *int_box,
+                                             const float *__restrict__ leaf_box, int32_t *size, TreeletShared &sh,
+                                             int lane) {
     const int32_t node = __builtin_amdgcn_readfirstlane(*order_at);
     uint32_t w[8];
 #pragma unroll
@@ -2116,16 +2122,18 @@ __device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *l
     if (c0 < 0 && c1 < 0) return;  // two leaves: one topology, nothing to change
     // this lane's treelet leaf, its children and box, and its area's bits if
     // it can be opened (areas are not negative; -1: it cannot)
-    int32_t c = lane == 0 ? c0 : c1, cl = 0, cr = 0, key = -1, op = 0x7FFFFFFF;
+    int32_t c = lane == 0 ? c0 : c1, cl = 0, cr = 0, key = -1, op = 0x7FFFFFFF, below = 0;
     float b[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     auto join = [&]() {
         const float *p = c < 0 ? leaf_box + 6 * (int64_t)(-c - 1) : int_box + 6 * (int64_t)c;
 #pragma unroll
         for (int q = 0; q < 6; ++q) b[q] = p[q];
         key = -1;
+        below = 1;
         if (c >= 0) {
             cl = left[c];
             cr = right[c];
+            below = size[c];
             const float a = area32(b, b + 3);
             if (a >= 0.0f) key = __float_as_int(a);
         }
@@ -2231,6 +2239,12 @@ __device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *l
         nb[q] = myT & 64u ? a6 : a;
         nb[3 + q] = myT & 64u ? z6 : z;
     }
+    int32_t leaves_below = 0;
+#pragma unroll
+    for (int k = 0; k < kTreelet; ++k) {
+        const int32_t b_k = __builtin_amdgcn_readlane(below, k);
+        leaves_below += (myT >> k) & 1u ? b_k : 0;
+    }
     if (lane < m - 1) {
         const int32_t me = lane == 0 ? node : in_me;
         const int32_t l = np == 1 ? leaf_l : in_l, r = (R & (R - 1u)) == 0u ? leaf_r : in_r;
@@ -2241,6 +2255,7 @@ __device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *l
         if (r < 0) parent_leaf[-r - 1] = me;
         else parent_int[r] = me;
         if (lane > 0) {
+            size[me] = leaves_below;
             float *p = int_box + 6 * (int64_t)me;
 #pragma unroll
             for (int q = 0; q < 6; ++q) p[q] = nb[q];
@@ -2251,9 +2266,9 @@ __device__ __forceinline__ void treelet_node(const int32_t *order_at, int32_t *l
 // The nodes of one depth, a wave each.
 __global__ void __launch_bounds__(64)
 k_treelet(const int32_t *__restrict__ order, int32_t *left, int32_t *right, int32_t *parent_int, int32_t *parent_leaf,
-          float *int_box, const float *__restrict__ leaf_box) {
+          float *int_box, const float *__restrict__ leaf_box, int32_t *size) {
     __shared__ TreeletShared sh;
-    treelet_node(order + blockIdx.x, left, right, parent_int, parent_leaf, int_box, leaf_box, sh, threadIdx.x);
+    treelet_node(order + blockIdx.x, left, right, parent_int, parent_leaf, int_box, leaf_box, size, sh, threadIdx.x);
 }
 
 // The nodes of the depths `from` .. 0 in one workgroup, for depths of at most
@@ -2267,13 +2282,13 @@ __global__ void __launch_bounds__(64 * kTopWaves) k_treelet_top(const int32_t *_
                                                                 const uint32_t *__restrict__ hcount, int from,
                                                                 int32_t *left, int32_t *right, int32_t *parent_int,
                                                                 int32_t *parent_leaf, float *int_box,
-                                                                const float *__restrict__ leaf_box) {
+                                                                const float *__restrict__ leaf_box, int32_t *size) {
     __shared__ TreeletShared sh[kTopWaves];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     for (int d = from; d >= 0; --d) {
         const uint32_t at = hstart[d], n = hcount[d];
         for (uint32_t i = (uint32_t)wave; i < n; i += kTopWaves)
-            treelet_node(order + at + i, left, right, parent_int, parent_leaf, int_box, leaf_box, sh[wave], lane);
+            treelet_node(order + at + i, left, right, parent_int, parent_leaf, int_box, leaf_box, size, sh[wave], lane);
         __syncthreads();
     }
 }
@@ -2799,11 +2814,8 @@ int64_t top_depths(const DepthOrder &o, uint32_t most) {
     return d;
 }
 
-// Renumbers the leaves of the binary hierarchy in s (n >= 2) in the tree's
-// left-to-right order: triangle order ids -> ids_out, leaf boxes to box_out
-// (which then replaces s.leaf_box), inner leaf ranges first / last.
-rg_status relabel_leaves(LbvhScratch &s, int64_t n, const uint32_t *ids, uint32_t *ids_out, float *box_out,
-                         hipStream_t st) {
+// s.size, the leaves below every inner node, by depth.
+rg_status subtree_sizes(LbvhScratch &s, int64_t n, hipStream_t st) {
     DepthOrder o;
     rg_status r = depth_order(s, n - 1, st, o);
     if (r != RG_OK) return r;
@@ -2813,6 +2825,16 @@ rg_status relabel_leaves(LbvhScratch &s, int64_t n, const uint32_t *ids, uint32_
                                                                         s.right, s.size);
     k_sizes_top<<<1, 1024, 0, st>>>(s.order, s.hstart, s.hcount, (int)top, s.left, s.right, s.size);
     RG_LAUNCH_CHECK();
+    return RG_OK;
+}
+
+// Renumbers the leaves of the binary hierarchy in s (n >= 2) in the tree's
+// left-to-right order: triangle order ids -> ids_out, leaf boxes to box_out
+// (which then replaces s.leaf_box), inner leaf ranges first / last.
+rg_status relabel_leaves(LbvhScratch &s, int64_t n, const uint32_t *ids, uint32_t *ids_out, float *box_out,
+                         bool have_sizes, hipStream_t st) {
+    rg_status r = have_sizes ? RG_OK : subtree_sizes(s, n, st);
+    if (r != RG_OK) return r;
     k_ploc_ranks<<<rg_blocks(n, kThreads), kThreads, 0, st>>>(n, s.left, s.pint, s.pleaf, s.size, ids,
                                                                s.leaf_box, s.rank, s.first, s.last, ids_out,
                                                                box_out);
@@ -2855,7 +2877,7 @@ rg_status ploc_build(const float *prim_box, int64_t n, int radius, const uint32_
         cur ^= 1;
     }
     if (next != -1) return RG_ERR_HIP;
-    return relabel_leaves(s, n, ids, ids_out, s.cbox[cur], st);
+    return relabel_leaves(s, n, ids, ids_out, s.cbox[cur], false, st);
 }
 
 // Rounds of treelet restructuring over the binary hierarchy in s (n >= 2),
@@ -2873,12 +2895,12 @@ rg_status treelet_build(int64_t n, int rounds, const uint32_t *ids, uint32_t *id
         const int64_t top = top_depths(o, kTreeletTop);
         for (int64_t d = o.dmax; d > top; --d)
             k_treelet<<<o.cnt[d], 64, 0, st>>>(s.order + o.start[d], s.left, s.right, s.pint, s.pleaf, s.int_box,
-                                               s.leaf_box);
+                                               s.leaf_box, s.size);
         k_treelet_top<<<1, 64 * kTopWaves, 0, st>>>(s.order, s.hstart, s.hcount, (int)top, s.left, s.right, s.pint,
-                                                    s.pleaf, s.int_box, s.leaf_box);
+                                                    s.pleaf, s.int_box, s.leaf_box, s.size);
         RG_LAUNCH_CHECK();
     }
-    return relabel_leaves(s, n, ids, ids_out, s.cbox[0], st);
+    return relabel_leaves(s, n, ids, ids_out, s.cbox[0], true, st);
 }
 
 // A level-by-level collapse between host reads.  Levels go in batches; the
@@ -3090,6 +3112,7 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
         // where the launches below take 150 for 64 primitives as for 1,024
         SmallArgs sa = small_args(nullptr, nullptr, nullptr);
         sa.tree_out = true;
+        sa.size = s.size;
         k_small_build<2, true><<<1, kSmallThreads, small_lds_bytes(n), st>>>(sa);
         RG_LAUNCH_CHECK();
     } else {
@@ -3139,7 +3162,8 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
                 for (int j0 = 0; j0 < top; j0 += kRangeStride)
                     k_range_levels<<<rg_blocks(kRangeStride * nbr, kThreads), kThreads, 0, st>>>(s.rtab, nbr, j0, top);
                 k_range_boxes<<<rg_blocks(n - 1, kThreads), kThreads, 0, st>>>(s.first, s.last, n - 1, s.leaf_box,
-                                                                                s.pre, s.suf, s.rtab, nbr, s.int_box);
+                                                                                s.pre, s.suf, s.rtab, nbr, s.int_box,
+                                                                                builder == RG_BUILDER_TREELET ? s.size : nullptr);
                 RG_LAUNCH_CHECK();
             }
         }
