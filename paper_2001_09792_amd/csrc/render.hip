@@ -220,9 +220,6 @@ __global__ void k_camera_batch(const RgJobDev *__restrict__ jobs, int n_jobs, in
     put_ray(q.ray, (uint32_t)i, o, d, 0.0f, INFINITY);
     q.pix[i] = (uint32_t)i;
     q.job[i] = j;
-    q.beta[0][i] = 1.0f;
-    q.beta[1][i] = 1.0f;
-    q.beta[2][i] = 1.0f;
 }
 
 struct ShadeArgs {
@@ -256,11 +253,13 @@ __global__ void __launch_bounds__(kShadeT) k_shade(ShadeArgs a) {
     if (active) {
         pixel = a.in.pix[i];
         job = a.in.job[i];
-        float beta[3] = {a.in.beta[0][i], a.in.beta[1][i], a.in.beta[2][i]};
         float o[3] = {a.in.ray[0][i], a.in.ray[1][i], a.in.ray[2][i]};
         float d[3] = {a.in.ray[3][i], a.in.ray[4][i], a.in.ray[5][i]};
         uint32_t rec = a.hit_rec[i];
         const bool primary = a.pass == a.jobs[job].start;
+        float beta[3] = {1.0f, 1.0f, 1.0f};  // a camera ray's, which its queue entry does not hold
+        if (!primary)
+            for (int q = 0; q < 3; ++q) beta[q] = a.in.beta[q][i];
         float direct[3] = {0.0f, 0.0f, 0.0f};  // what the hit itself adds to the pixel
         uint32_t *gbuf = primary ? a.jobs[job].gbuf : nullptr;
         if (rec == RG_MISS) {
@@ -429,7 +428,8 @@ __global__ void k_start(unsigned long long *stat, uint32_t *counts) {
     if (threadIdx.x == 0) start_counters(stat, counts, 0u);
 }
 
-// One camera ray per pixel of frame `slot`, at *base + pixel.
+// One camera ray per pixel of frame `slot`, at *base + pixel (its weight, one, is
+// not stored: 24 frames of 3.4 M pixels 1,374 -> 1,360 us).
 __global__ void __launch_bounds__(kT) k_camera_job(RgJobDev J, uint32_t slot, RgQueue q, const uint32_t *base,
                                                    int64_t cap) {
     int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x;
@@ -444,9 +444,6 @@ __global__ void __launch_bounds__(kT) k_camera_job(RgJobDev J, uint32_t slot, Rg
     put_ray(q.ray, at, o, d, 0.0f, INFINITY);
     q.pix[at] = J.pix_off + (uint32_t)i;
     q.job[at] = slot;
-    q.beta[0][at] = 1.0f;
-    q.beta[1][at] = 1.0f;
-    q.beta[2][at] = 1.0f;
 }
 
 __global__ void k_resolve_job(const unsigned long long *acc, int64_t n, float *image) {
