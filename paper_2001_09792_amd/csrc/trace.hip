@@ -16,7 +16,7 @@ namespace {
 // and written out when all its rays are in.  A packet that still has a ray in
 // flight when its slot is needed again (a straggler) is written out as far as
 // it got; its late rays then store their results directly.
-constexpr int kStageSlots = 4;
+using rgt::kStageSlots;
 // What a kernel variant holds: the persistent traversal with a ray per lane,
 // the one with a group of lanes per ray (trace_groups), or both, the kernel
 // choosing by the number of rays it finds.  A launch of up to kGroupRays rays
@@ -42,11 +42,6 @@ struct StageShape {
                              : MODE == rgt::kRender ? (ANY ? 1 : 3)
                                                     : (ANY ? 3 : 2);
 };
-// LDS bytes per wave of the staging ring
-template <int K>
-constexpr size_t stage_wave_bytes() {
-    return (size_t)kStageSlots * (K * 64 * 4 + 16);  // words, then mask, owner and packet per slot
-}
 // Orders one wave's LDS accesses across lanes: a compiler fence at
 // wavefront scope and a wave barrier (the LDS serves a wave's accesses in
 // order).
@@ -128,22 +123,6 @@ __global__ void __launch_bounds__(rgt::kThreads) __attribute__((amdgpu_waves_per
         tr.call_cull = a.ray_flags & (RG_RAY_CULL_BACK | RG_RAY_CULL_FRONT);
         tr.rmask = a.mask;
     }
-    // this wave's staging ring: words [slot][K][64], mask [slot], owner
-    // [slot] (packet number q in the wave's sequence, ~0u: free), packet
-    // [slot] (the launch's packet that q stands for)
-    char RG_LDS *ring = (char RG_LDS *)&lds_stack[lds_depth * rgt::kThreads] + wib * stage_wave_bytes<K>();
-    uint32_t RG_LDS *sw = (uint32_t RG_LDS *)ring;
-    uint64_t RG_LDS *smask = (uint64_t RG_LDS *)(ring + kStageSlots * K * 64 * 4);
-    uint32_t RG_LDS *sown = (uint32_t RG_LDS *)(ring + kStageSlots * (K * 64 * 4 + 8));
-    uint32_t RG_LDS *spkt = (uint32_t RG_LDS *)(ring + kStageSlots * (K * 64 * 4 + 12));
-    if (lane < kStageSlots) {
-        sown[lane] = ~0u;
-        smask[lane] = 0ull;
-        spkt[lane] = ~0u;
-    }
-    wave_sync();
-    uint32_t ahead = 0u;  // lane 0: the claimed packet for the wave's next claimed packet number
-    if (lane == 0 && n_static < n_packets) ahead = atomicAdd(a.work, 1u);
     uint32_t q_end = 0u;   // packet numbers below this one have their packet (uniform)
     bool out_of_work = false;  // a claim came back past the last packet (uniform)
     uint32_t next = 0;   // position in this wave's ray sequence (the same in all lanes)
@@ -204,7 +183,7 @@ __global__ void __launch_bounds__(rgt::kThreads) __attribute__((amdgpu_waves_per
         if (PATH == kGroups || n <= n_waves * (64u / W) * kGroupRays) {
             // group stacks overlay the lane stacks and the staging rings
             rgt::trace_groups(tr, wave * per_wave, min(n, (wave + 1u) * per_wave),
-                              (uint32_t RG_LDS *)lds_stack + wib * (64u / W) * rgt::kStackCap, take_ray,
+                              (uint32_t RG_LDS *)lds_stack + wib * (uint32_t)(rgt::group_stacks_at(W, 1) / 4), take_ray,
                               [&](uint32_t i) {
 #pragma unroll
                                   for (int w = 0; w < K; ++w) store(w, i, word(w));
@@ -213,6 +192,23 @@ __global__ void __launch_bounds__(rgt::kThreads) __attribute__((amdgpu_waves_per
         }
     }
     if constexpr (PATH == kGroups) return;
+    // this wave's staging ring: words [slot][K][64], mask [slot], owner
+    // [slot] (packet number q in the wave's sequence, ~0u: free), packet
+    // [slot] (the launch's packet that q stands for).  Set up only here: a
+    // workgroup that has taken groups above keeps their stacks in these bytes
+    char RG_LDS *ring = (char RG_LDS *)lds_stack + (uint32_t)rgt::ring_at(K, lds_depth, (int)wib);
+    uint32_t RG_LDS *sw = (uint32_t RG_LDS *)ring;
+    uint64_t RG_LDS *smask = (uint64_t RG_LDS *)(ring + kStageSlots * K * 64 * 4);
+    uint32_t RG_LDS *sown = (uint32_t RG_LDS *)(ring + kStageSlots * (K * 64 * 4 + 8));
+    uint32_t RG_LDS *spkt = (uint32_t RG_LDS *)(ring + kStageSlots * (K * 64 * 4 + 12));
+    if (lane < kStageSlots) {
+        sown[lane] = ~0u;
+        smask[lane] = 0ull;
+        spkt[lane] = ~0u;
+    }
+    wave_sync();
+    uint32_t ahead = 0u;  // lane 0: the claimed packet for the wave's next claimed packet number
+    if (lane == 0 && n_static < n_packets) ahead = atomicAdd(a.work, 1u);
     // Writes slot s's staged rays, those of launch packet pkt (all lanes
     // together; uniform arguments).
     auto flush_slot = [&](int s, uint32_t pkt, uint64_t m) {
@@ -507,7 +503,7 @@ template <int W, bool ANY, int MODE, bool OPT, int PATH>
 void launch_path(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
     auto kernel = k_trace<W, ANY, MODE, OPT, PATH>;
     if (PATH != kLanes) {
-        const size_t groups = (size_t)(rgt::kThreads / W) * rgt::kStackCap * sizeof(uint32_t);
+        const size_t groups = rgt::groups_bytes(W);
         shm = PATH == kGroups || shm < groups ? groups : shm;
     }
     blocks = resident_cap(kernel, blocks, shm);
@@ -595,8 +591,7 @@ rg_status launch_w(bool any, int mode, const RgTraceArgs &a, hipStream_t st, con
     unsigned blocks = persistent_blocks(a.n, t.waves_per_cu);
     // the traversal stacks, then one staging ring per wave
     const int K = mode == rgt::kCounts ? 0 : (mode == rgt::kRender ? (any ? 1 : 3) : (any ? 3 : 2));
-    size_t shm = (size_t)t.lds_depth * rgt::kThreads * sizeof(uint32_t) +
-                 (rgt::kThreads / 64) * (size_t)kStageSlots * (K * 64 * 4 + 16);
+    const size_t shm = rgt::lanes_bytes(K, t.lds_depth);
     if (a.opt) launch_mode<W, true>(any, mode, a, st, blocks, shm, t);
     else launch_mode<W, false>(any, mode, a, st, blocks, shm, t);
     RG_LAUNCH_CHECK();

@@ -20,13 +20,10 @@
 #pragma once
 
 #include "rg_internal.h"
+#include "trace_lds.h"
 
 namespace rgt {
 
-constexpr int kThreads = 256;     // threads per workgroup of the trace kernels
-constexpr int kMaxLdsStack = 32;  // most stack entries per lane kept in LDS (chosen per launch)
-constexpr int kPrivStack = 96;    // further entries per lane in private memory
-constexpr int kStackCap = 8 + kPrivStack;  // guaranteed capacity (at the smallest LDS depth, 8)
 constexpr uint32_t kFlip = 4u;  // in Tracer::cull: the instance flips its facing
 // rounds a wave may run without any of its rays finishing: far above any
 // traversal of a valid hierarchy (a loop bound, not a limit of the method)
