@@ -2534,8 +2534,34 @@ __global__ void __launch_bounds__(kThreads) k_refit_level(RefitJobs jobs, int le
 // Levels wider than kRefitTopNodes leave the one compute unit behind: 16
 // bottom levels of 156,800 triangles took 45 us for the levels of up to 4,096
 // nodes, and take 26 us with those of 1,024 and 4,096 in launches of their own.
-constexpr int kRefitTopThreads = 256;
+// The bound W^l is far above what a small structure holds, though, and there
+// a launch per level costs more than the level: as long as the levels below
+// hold no more than refit_level_nodes each on average, they join the one
+// launch.  One mesh, every level below W^l = 256 in its own launch -> one
+// launch: W = 2, 800 triangles 40 -> 29 us, 1,600 42 -> 32, 3,200 56 -> 44;
+// W = 4, 2,000 triangles 39 -> 32 (four of them), 6,400 in leaves of four 47
+// -> 43; beyond, W = 4, 3,200 triangles in two levels (750 nodes each) 30 ->
+// 34, 12,800 in leaves of four (510 each) 58 -> 64.  Width 8, whose nodes take
+// longest: 800 triangles 24.7 -> 23.7, at 410 nodes a level 33 -> 34.  (512
+// threads: with 256 the same meshes take 30, 36, 49, 32 and 45 us.)
+constexpr int kRefitTopThreads = 512;
 constexpr uint32_t kRefitTopNodes = 256;  // the widest level the one-workgroup launch takes (W^l)
+constexpr int64_t refit_level_nodes(int W) { return W == 8 ? 320 : 480; }
+
+// Levels 0 .. the result - 1 of hierarchies of up to max_nodes nodes and
+// max_depth levels go into the one-workgroup launch.
+constexpr int refit_top_levels(int W, int max_depth, int64_t max_nodes) {
+    int top = 1;
+    for (uint64_t c = (uint64_t)W; c <= kRefitTopNodes && top < max_depth; c *= (uint64_t)W) ++top;
+    return max_nodes <= refit_level_nodes(W) * (max_depth - top) ? max_depth : top;
+}
+static_assert(refit_top_levels(2, 14, 999) == 14 && refit_top_levels(2, 16, 3199) == 16 &&
+                  refit_top_levels(4, 8, 1399) == 8 && refit_top_levels(8, 4, 278) == 4,
+              "structures of up to some thousand triangles: one launch");
+static_assert(refit_top_levels(2, 21, 29999) == 9 && refit_top_levels(4, 7, 1497) == 5 &&
+                  refit_top_levels(4, 9, 3869) == 5 && refit_top_levels(8, 6, 2899) == 3,
+              "wide levels: a launch each");
+
 template <int W>
 __global__ void __launch_bounds__(kRefitTopThreads) k_refit_top(RefitJobs jobs, int top) {
     const RefitJob &J = jobs.j[blockIdx.x];
@@ -2624,10 +2650,8 @@ __global__ void k_refit_up(RgNode<W> *nodes, int64_t n_nodes, const uint32_t *__
 }
 
 template <int W>
-void refit_levels(const RefitJobs &jobs, int n, int max_depth, unsigned blocks, hipStream_t st) {
-    // levels 0 .. top - 1 hold at most W^(top - 1) <= kRefitTopNodes nodes
-    int top = 1;
-    for (uint64_t c = W; c <= kRefitTopNodes && top < max_depth; c *= W) ++top;
+void refit_levels(const RefitJobs &jobs, int n, int max_depth, int64_t max_nodes, unsigned blocks, hipStream_t st) {
+    const int top = refit_top_levels(W, max_depth, max_nodes);
     for (int l = max_depth - 1; l >= top; --l)
         k_refit_level<W><<<dim3(blocks, (unsigned)n), kThreads, 0, st>>>(jobs, l);
     k_refit_top<W><<<(unsigned)n, kRefitTopThreads, 0, st>>>(jobs, top);
@@ -3634,9 +3658,9 @@ rg_status rg_refit_blas_many(rg_blas *blas, int32_t n_blas, const float *const *
         unsigned lb = rg_blocks(max_nodes, kThreads);
         if (lb > 512) lb = 512;
         if (max_depth > 0) {
-            if (w == 2) refit_levels<2>(jobs, n, max_depth, lb, st);
-            else if (w == 4) refit_levels<4>(jobs, n, max_depth, lb, st);
-            else refit_levels<8>(jobs, n, max_depth, lb, st);
+            if (w == 2) refit_levels<2>(jobs, n, max_depth, max_nodes, lb, st);
+            else if (w == 4) refit_levels<4>(jobs, n, max_depth, max_nodes, lb, st);
+            else refit_levels<8>(jobs, n, max_depth, max_nodes, lb, st);
         }
         RG_LAUNCH_CHECK();
         for (int k = 0; k < n; ++k) {
