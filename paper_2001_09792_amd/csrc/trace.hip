@@ -17,6 +17,7 @@ namespace {
 // flight when its slot is needed again (a straggler) is written out as far as
 // it got; its late rays then store their results directly.
 using rgt::kStageSlots;
+using rgt::wave_sync;
 // What a kernel variant holds: the persistent traversal with a ray per lane,
 // the one with a group of lanes per ray (trace_groups), or both, the kernel
 // choosing by the number of rays it finds.  A launch of up to kGroupRays rays
@@ -42,14 +43,6 @@ struct StageShape {
                              : MODE == rgt::kRender ? (ANY ? 1 : 3)
                                                     : (ANY ? 3 : 2);
 };
-// Orders one wave's LDS accesses across lanes: a compiler fence at
-// wavefront scope and a wave barrier (the LDS serves a wave's accesses in
-// order).
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // A wave-uniform 64-bit value in scalar registers.  readfirstlane gives an
 // int: each half goes through uint32_t, or a set bit 31 of the low half would
 // fill the high half with ones.

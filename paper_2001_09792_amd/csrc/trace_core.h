@@ -568,6 +568,14 @@ struct Tracer {
     }
 };
 
+// Orders one wave's LDS accesses across lanes: a compiler fence at
+// wavefront scope and a wave barrier (the LDS serves a wave's accesses in
+// order).  The barrier alone orders no memory.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Value of the lane at `ctrl` (DPP: quad_perm, row_half_mirror); every lane
 // read from is active.
 template <int CTRL>
@@ -732,7 +740,7 @@ __device__ inline void trace_groups(Tracer<W, ANY, MODE, OPT> &tr, uint32_t firs
             }
             if (lane_in(m_leaf)) tr.cur = count > (uint32_t)W ? tr.cur - ((uint32_t)W << 28) + (uint32_t)W : RG_EMPTY;
         }
-        __builtin_amdgcn_wave_barrier();  // the group's pushes come before its pops
+        wave_sync();  // the group's pushes come before its pops
         uint64_t pop = ballot(tr.cur == RG_EMPTY) & has & ~stop;
         const uint64_t end = ballot(tr.st.sp == 0) & pop;
         pop &= ~end;
@@ -743,6 +751,7 @@ __device__ inline void trace_groups(Tracer<W, ANY, MODE, OPT> &tr, uint32_t firs
         }
         blas &= ~leave;
         if (lane_in(pop)) tr.cur = stk[--tr.st.sp];
+        wave_sync();  // and its pops before the next round's pushes
         uint64_t fin = end | stop;
         // loop bound: see Tracer's callers
         stalled = fin ? 0u : stalled + 1u;
