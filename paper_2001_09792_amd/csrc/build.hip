@@ -1785,9 +1785,11 @@ constexpr int kTreeletMaxRounds = 8;
 constexpr int kSplitLanes[kTreelet + 1] = {0, 0, 0, 1, 1, 2, 8, 64};
 constexpr int kSplitIts[kTreelet + 1] = {0, 0, 0, 3, 7, 8, 4, 1};
 constexpr int kSplitByte[kTreelet + 1] = {0, 0, 0, 4, 7, 14, 22, 26};  // the lane's splits of a level
-struct TreeletSchedule {
+// (rows are read as words, 16 bytes at a time)
+struct alignas(16) TreeletSchedule {
     uint8_t b[64][32];  // 0 .. 3: the lane's subset at sizes 3 .. 6 (0: none), then its splits by size
 };
+static_assert(alignof(TreeletSchedule) % 16 == 0 && sizeof(TreeletSchedule::b[0]) % 16 == 0, "row alignment");
 
 constexpr int popc_const(int v) { return v ? (v & 1) + popc_const(v >> 1) : 0; }
 
