@@ -272,7 +272,8 @@ def optimal_treelet(lo: np.ndarray, hi: np.ndarray):
     not change), by dynamic programming over the subsets S of the leaves:
     cost(S) = 0 for one leaf, else area(S) + min over the splits (P, S \\ P)
     of cost(P) + cost(S \\ P), P holding the lowest leaf of S and enumerated
-    in increasing bit order, the first minimum kept; every sum float32.
+    in increasing bit order, the first minimum kept (where every sum is
+    infinite, the first split); every sum float32.
     Returns cost, split (per subset bit mask) and the union boxes."""
     m = lo.shape[0]
     full = (1 << m) - 1
@@ -291,7 +292,7 @@ def optimal_treelet(lo: np.ndarray, hi: np.ndarray):
             continue
         low = S & -S
         rest = S ^ low
-        best, bp = np.float32(np.inf), 0
+        best, bp = np.float32(np.inf), low
         Q = 0
         while True:
             P = low | Q
