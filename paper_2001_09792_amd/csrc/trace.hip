@@ -20,20 +20,27 @@ using rgt::kStageSlots;
 using rgt::wave_sync;
 // What a kernel variant holds: the persistent traversal with a ray per lane,
 // the one with a group of lanes per ray (trace_groups), or both, the kernel
-// choosing by the number of rays it finds.  A launch of up to kGroupRays rays
-// per resident group takes groups (two-level scene, width 4, random rays, a
+// choosing by the number of rays it finds.  A launch of up to two rays per
+// resident group takes groups (two-level scene, width 4, random rays, a
 // lane per ray / groups at 1, 2, 3 rays per group: 1,000 rays 46.7 / 38.1 /
 // 37.3 / 37.5 us, 16,384 rays 84.6 / 66.2 / 65.4 / 65.4, 100,000 rays 99.7 /
 // 100.2 / 91.8 / 92.1; a 256x256 frame 182 / 139 / 138 / 138, a 1080p depth-4
-// frame at width 8 1,468 / 1,383 / 1,374 / 1,414).  A launch whose size the
+// frame at width 8 1,468 / 1,383 / 1,374 / 1,414; frames of 131,406 to 161,000
+// pixels, width 4, 2.01 to 2.46 rays per group: lanes 222 to 250 us, groups
+// 236 to 286).  At width 8 the line lies at two and a quarter (random rays
+// there: lanes 97 to 129 us, groups 84 to 94; frames of 75,600 and 81,225
+// pixels, 2.3 and 2.5 per group: lanes 194 and 199 us, groups 213 and 227).
+// Width 2 keeps a lane per ray: a group of two would leave each lane most of
+// its round (no grouped form of it was measured).  A launch whose size the
 // host knows gets the variant it needs; a pass of a frame, whose size only
-// the device knows, the one with both.  That one holds 109 registers where
-// the plain one holds 95 (width 4), so the launches that are always long (the
+// the device knows, the one with both.  That one holds 112 registers where
+// the plain one holds 100 (width 4), so the launches that are always long (the
 // occlusion rays of a frame) and the engine's, which share the chip with the
 // launches of another stream and lose by groups (11.98 -> 12.56 ms for 24
 // requests), take the plain one.
 enum Path { kLanes = 0, kGroups = 1, kEither = 2 };
-constexpr uint32_t kGroupRays = 2;
+// most rays of a grouped launch, of `groups` resident groups of W lanes
+constexpr uint32_t group_rays(uint32_t groups, int W) { return 2u * groups + (W == 8 ? groups / 4u : 0u); }
 constexpr uint32_t kClaimMin = 16;  // packets per wave from which a launch claims its last quarter
 template <bool ANY, int MODE>
 struct StageShape {
@@ -173,7 +180,7 @@ __global__ void __launch_bounds__(rgt::kThreads) __attribute__((amdgpu_waves_per
         return live;
     };
     if constexpr (PATH != kLanes) {
-        if (PATH == kGroups || n <= n_waves * (64u / W) * kGroupRays) {
+        if (PATH == kGroups || n <= group_rays(n_waves * (64u / W), W)) {
             // group stacks overlay the lane stacks and the staging rings
             rgt::trace_groups(tr, wave * per_wave, min(n, (wave + 1u) * per_wave),
                               (uint32_t RG_LDS *)lds_stack + wib * (uint32_t)(rgt::group_stacks_at(W, 1) / 4), take_ray,
@@ -494,27 +501,32 @@ unsigned resident_cap(Kernel kernel, unsigned blocks, size_t shm) {
 
 template <int W, bool ANY, int MODE, bool OPT, int PATH>
 void launch_path(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
-    auto kernel = k_trace<W, ANY, MODE, OPT, PATH>;
-    if (PATH != kLanes) {
-        const size_t groups = rgt::groups_bytes(W);
-        shm = PATH == kGroups || shm < groups ? groups : shm;
-    }
-    blocks = resident_cap(kernel, blocks, shm);
-    kernel<<<blocks, rgt::kThreads, shm, st>>>(a, t.refill, t.lds_depth, t.leaf_batch, t.inst_batch);
+    k_trace<W, ANY, MODE, OPT, PATH><<<blocks, rgt::kThreads, shm, st>>>(a, t.refill, t.lds_depth, t.leaf_batch,
+                                                                         t.inst_batch);
 }
 
+// The path of a launch: groups for up to kGroupRays rays per resident group
+// (counted after resident_cap, as the kernel that chooses by itself counts).
 template <int W, bool ANY, int MODE, bool OPT>
 void launch_one(const RgTraceArgs &a, hipStream_t st, unsigned blocks, size_t shm, const rg_trace_tune &t) {
     if constexpr (W >= 4 && MODE != rgt::kCounts) {
         if (!a.lanes) {
-            const int64_t small = (int64_t)blocks * rgt::kThreads / W * kGroupRays;
-            if (a.n <= small) return launch_path<W, ANY, MODE, OPT, kGroups>(a, st, blocks, shm, t);
+            const auto most_rays = [](unsigned b) { return (int64_t)group_rays(b * (rgt::kThreads / W), W); };
+            const size_t groups = rgt::groups_bytes(W);
+            if (a.n <= most_rays(blocks)) {
+                const unsigned b = resident_cap(k_trace<W, ANY, MODE, OPT, kGroups>, blocks, groups);
+                if (a.n <= most_rays(b)) return launch_path<W, ANY, MODE, OPT, kGroups>(a, st, b, groups, t);
+            }
             if constexpr (MODE == rgt::kRender) {
-                if (a.count) return launch_path<W, ANY, MODE, OPT, kEither>(a, st, blocks, shm, t);
+                if (a.count) {
+                    const size_t most = shm < groups ? groups : shm;
+                    const unsigned b = resident_cap(k_trace<W, ANY, MODE, OPT, kEither>, blocks, most);
+                    return launch_path<W, ANY, MODE, OPT, kEither>(a, st, b, most, t);
+                }
             }
         }
     }
-    launch_path<W, ANY, MODE, OPT, kLanes>(a, st, blocks, shm, t);
+    launch_path<W, ANY, MODE, OPT, kLanes>(a, st, resident_cap(k_trace<W, ANY, MODE, OPT, kLanes>, blocks, shm), shm, t);
 }
 
 template <int W, bool OPT>
