@@ -48,7 +48,8 @@ SAH_C_NODE, SAH_C_TRI = 1.0, 1.0
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_ao_closest.json")
 # what the traversal kernel is compiled from (sources and compiler flags)
-KERNEL_SOURCES = ["paper_2001_09792_amd/csrc/trace_core.h", "paper_2001_09792_amd/csrc/trace.hip",
+KERNEL_SOURCES = ["paper_2001_09792_amd/csrc/trace_core.h", "paper_2001_09792_amd/csrc/trace_lds.h",
+                  "paper_2001_09792_amd/csrc/trace.hip",
                   "paper_2001_09792_amd/csrc/rg_internal.h", "paper_2001_09792_amd/csrc/build.hip",
                   "paper_2001_09792_amd/_build.py"]
 

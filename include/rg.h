@@ -470,7 +470,15 @@ rg_status rg_trace_counts(const rg_tlas *tlas, rg_rays rays, int64_t n, int32_t 
  * rest in private memory.  A wave runs its leaf code once leaf_batch (1..64)
  * lanes wait at a leaf and its instance-entry code once inst_batch (1..64)
  * lanes wait at an instance (or when no lane has other work); 1 runs them
- * whenever any lane needs them.  Results do not depend on any of these.
+ * whenever any lane needs them.  Both are taken as 1 where nothing is gained
+ * by waiting: in packets of fewer than 64 rays, and once a wave has taken its
+ * last rays.
+ * Short launches at widths 4 and 8 (up to 2 rays, at width 8 2.25, per group
+ * that stays resident; not the engine's, the occlusion rays' of an
+ * ambient-occlusion frame, nor rg_trace_counts') give each ray a group of
+ * `width` lanes instead.  They use waves_per_cu only: a group keeps its whole
+ * stack in LDS, takes its next ray by itself and waits for no other.
+ * Results do not depend on any of these.
  * Either pointer may be NULL.  Errors: RG_ERR_INVALID_ARG for an unknown
  * scope or values out of range. */
 typedef struct {
@@ -727,7 +735,8 @@ rg_status rg_engine_create(const rg_engine_desc *desc /*host*/, void *scratch, u
 rg_status rg_engine_destroy(rg_engine *engine);
 /* Admits a frame (mode 0) if its reservation fits: writes its record and
  * materials through kernel arguments (job->mats may go away on return),
- * zeroes its accumulators and queues its camera rays for the next pass.
+ * and queues its camera rays for the next pass, whose shading starts the
+ * frame's accumulators.
  * Lifetime: the frame's top level, the bottom levels it refers to and its
  * image are read and written by the engine's passes (on its stream and a
  * side stream of its own) until rg_engine_poll returns the frame's tag; the

@@ -313,11 +313,14 @@ __global__ void __launch_bounds__(kSortThreads) k_morton(const float *__restrict
 // all smaller digits plus the counts of the tiles before it: the scatter adds
 // them up itself, over whole groups of kSortGroup tiles and the tiles of its
 // own group, up to kSortDirect tiles -- 79 rows of 256 counts at most, which
-// arrive together.  Beyond that the rows would outweigh the keys, and a third
-// launch scans the counts (k_sort_scan, one workgroup per digit), 4 us each at
-// 627,200 keys.  A single launch per pass with a look-back over earlier tiles'
-// counts was slower here: with ~300 tiles finishing at once its chain of
-// cross-die reads outlasts the extra launches.
+// arrive together.  Beyond that a third launch scans the counts (k_sort_scan,
+// one workgroup per digit), 4 us each at 627,200 keys.  Whole linear builds
+// with the scan / without: 627,200 triangles 462 / 433 us, 1,500,000 671 /
+// 641, 2,093,058 (1,022 tiles) 849 / 819.  The rows outweigh the scan far
+// above the line only: 2,196,608 901 / 875, 3,998,792 1,403 / 1,366,
+// 5,999,648 1,978 / 1,976.  A single launch per pass with a look-back over
+// earlier tiles' counts was slower here: with ~300 tiles finishing at once its
+// chain of cross-die reads outlasts the extra launches.
 constexpr int kSortDirect = 1024;
 
 // Ranks a tile's items by digit, tile order = (wave, item, lane): rk[k] =
@@ -3144,7 +3147,9 @@ rg_status rg_lbvh_build(const float *prim_box, int64_t n, int32_t width, int32_t
     } else {
         const int nblocks = (int)((n + kSortTile - 1) / kSortTile);
         // centre bounds (partials; the sort's counters cleared), keys with the
-        // digit counts of every pass, then one launch per pass
+        // digit counts of every pass, then per pass the tiles' counts (the
+        // first's come with the keys), above kSortDirect tiles their scan,
+        // and the scatter
         int64_t bparts = (n + kThreads - 1) / kThreads;
         if (bparts > kBoundParts) bparts = kBoundParts;
         // the group counts of all passes lie where the wide-node plan goes later

@@ -9,9 +9,13 @@
 // normalising over them.  FXAA: Lottes' method (2009, "quality" variant) on
 // the perceptual luma sqrt(clamp(0.299 R + 0.587 G + 0.114 B, 0, 1)).
 //
-// Both are memory-bound stencils over float[h][w][3] images: one thread per
-// pixel, 64 x 4 pixel blocks, so that a wave reads one row segment; the blur
-// stages each block's pixels and their halo along its axis in LDS.
+// Both are stencils over float[h][w][3] images: one thread per pixel, 64 x 4
+// pixel blocks, so that a wave reads one row segment; the blur stages each
+// block's pixels and their halo along its axis in LDS.  Where most pixels are
+// blurred, the blur's time is its taps (17 LDS reads of 16 bytes at radius 8,
+// and an exponential and two masked updates of four sums per distance); where
+// the image is dense in edges, FXAA's is the four texels of each search step,
+// two of which have weight zero in the five unit steps.
 #include "rg_internal.h"
 
 namespace {

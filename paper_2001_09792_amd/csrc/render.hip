@@ -9,9 +9,9 @@
 // is (pixel, throughput).  Shading adds the sky on a miss and the ambient
 // term on a diffuse hit to the pixel, queues a shadow ray carrying the
 // pending direct term, and queues mirror / glass children.  Children and
-// shadow rays are appended with one atomic per wave (ballot + popcount
-// ranks).  Pixel sums are 64-bit fixed point (2^32 per unit), so the image
-// is independent of the order in which waves append and add.
+// shadow rays are appended with one atomic per block for both queues (ballot
+// + popcount ranks).  Pixel sums are 64-bit fixed point (2^32 per unit), so
+// the image is independent of the order in which blocks append and add.
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -1263,8 +1263,8 @@ extern "C" rg_status rg_render_static(const rg_tlas *tlas, const rg_material *ma
     }
     void *p = nullptr;
     if ((r = static_scratch(&p)) != RG_OK) return r;
-    // the same passes as rg_render; every counter, statistic and accumulator
-    // that must start at zero is cleared by the passes' own fill kernels
+    // the same passes as rg_render: the first launch starts the counters and
+    // statistics, and each pixel's sums start with its camera ray's shading
     return rg_render_ex(tlas, mats, n_mats, cam, light, width, height, max_depth, mode, seed, image, nullptr, p,
                         RG_STATIC_SCRATCH_BYTES, stream, nullptr);
 }

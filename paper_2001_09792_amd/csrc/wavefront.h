@@ -71,11 +71,12 @@ rg_status rg_wave_reset(const RgWaveBufs &b, hipStream_t st);
 
 // Writes frame record `slot` (and its top-level reference) and n_mats
 // materials at b.mats + J.mat_off, through kernel arguments, so the host
-// arrays may go away when this returns and nothing waits; zeroes the
-// frame's accumulators and appends its camera rays (one per pixel) to ray
-// queue `queue`.  Two launches (and one per 64 materials beyond the first
-// 64).  first: the only frame of a render; the statistics and the counters
-// start over with its rays (no rg_wave_reset needed).
+// arrays may go away when this returns and nothing waits; appends the
+// frame's camera rays (one per pixel) to ray queue `queue`.  The accumulators
+// are left as they are: shading a camera ray starts its pixel's sums.  Two
+// launches (and one per 64 materials beyond the first 64).  first: the only
+// frame of a render; the statistics and the counters start over with its rays
+// (no rg_wave_reset needed).
 rg_status rg_wave_put_frame(const RgWaveBufs &b, uint32_t slot, const RgJobDev &J, const RgTlasRef &T,
                             const rg_material *host_mats, int32_t n_mats, bool first, int queue, hipStream_t st);
 
